@@ -286,16 +286,18 @@ int tl_gemm_plan(int64_t M, int64_t N, int64_t K, const tl_layout_desc* layout,
  *                total_rows; read by the kernel, clamped to [0, total_rows].
  *                Out-of-order offsets give unspecified rows of C, never an
  *                access outside A, W or C.
- * max_group_rows: host bound on the rows of one group; it picks the kernel's
- *                M tile (16, 32 or 64 rows).  A group with more rows is
+ * max_group_rows: host bound on the rows of one group; it picks the kernel and
+ *                its M tile: the decode kernel with 16 rows up to 16 (32 or 64
+ *                where a tile is requested), above that the row-adaptive
+ *                kernel with up to 256 rows.  A group with more rows is
  *                processed in several passes over its weight (correct, more
  *                traffic).
  * W:             device, group_stride bytes apart (a multiple of 16, at least
  *                one weight: tl_tile_bytes for tile-major, N * K * 2 else).
  * C:             device [total_rows][N] row-major, fp32 or bf16 per
  *                layout->out_dtype; rows of empty groups are not written.
- * Weights stream once per group and pass (4-wave workgroups, one per (group,
- * tile_n-row tile), K not split), so results match tl_gemm to rounding.
+ * Weights stream once per group and pass (one workgroup per group, row pass
+ * and tile of weight rows, K not split), so results match tl_gemm to rounding.
  * fetch_mode: as tl_gemm (TL_FETCH_BLOCK on NK_ROW is not supported here).
  * Errors: TL_EINVAL for num_groups < 1, total_rows < 0, a_rows < 1, rows
  * beyond 2^31 - 1, a short or misaligned group_stride, NULL or misaligned
@@ -320,8 +322,8 @@ int tl_gemm_grouped(const void* A, int64_t a_rows, const int32_t* token_ids,
  * for rows r of group e as in tl_gemm_grouped (t = token_ids[r] or r), with
  * silu(x) = x / (1 + e^-x) evaluated in fp32 on the fp32 sums.  H: device
  * [total_rows][I] row-major, fp32 or bf16 per layout->out_dtype.  Every
- * workgroup reads 32 gate rows and the 32 matching up rows -- whole memory
- * tiles when block_rows divides 32 -- so the [total_rows][2I] projection is
+ * workgroup reads groups of 32 gate rows and the 32 matching up rows -- whole
+ * memory tiles when block_rows divides 32 -- so the [total_rows][2I] projection is
  * never written.  Arguments, ownership and errors as tl_gemm_grouped with
  * N = I for C and 2I weight rows (group_stride >= the bytes of a [2I][K]
  * weight: tl_tile_bytes(2I, K, ...) for tile-major); in addition

@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "tl_internal.h"
+#include "tl_medium.h"
 
 namespace tl {
 
@@ -616,6 +617,62 @@ int plan_grouped(int64_t max_group_rows, int64_t N, int64_t K, const tl_layout_d
     return TL_OK;
 }
 
+// Weight and layout fields of a row-adaptive launch (tl_medium.hip).
+MediumParams medium_params(const Plan& p, const void* A, const void* W, void* C, int64_t N, int64_t K,
+                           MediumConfig cfg, bool swiglu) {
+    const bool tile = p.L.kind == TL_LAYOUT_TILE;
+    const int64_t cols = medium_tile_n(cfg) / (swiglu ? 2 : 1);
+    MediumParams m;
+    m.A = static_cast<const uint16_t*>(A);
+    m.W = static_cast<const uint8_t*>(W);
+    m.C = C;
+    m.N = int(N);
+    m.K = int(K);
+    m.strip_bytes = tile ? p.L.br * padded_cols(p.L, K) * 2 : 0;
+    m.log2_br = tile ? p.L.log2_br : 0;
+    m.log2_bc = tile ? p.L.log2_bc : 0;
+    m.log2_G = tile ? p.L.log2_G : 0;
+    m.bc_mask = tile ? int(p.L.bc - 1) : 0;
+    m.out_bf16 = p.out_bf16;
+    m.n_tiles = int((N + cols - 1) / cols);
+    return m;
+}
+
+// Whether a grouped launch takes the row-adaptive kernel, its configuration
+// and its grid.  It does when a group may exceed one 16-row MFMA tile of the
+// decode kernel (which streams a group's weight once per 64 rows and reloads
+// the activations for every 64 weight rows) and no tile is requested:
+// measured over 60 shapes of 16 - 128 experts, groups of up to 17 - 552 rows
+// run 1.0 - 4.2x faster, and at up to 16 rows the two are equal (within 3 %),
+// where the decode kernel stays.  Configurations, both sides from that sweep:
+//  - 256 x 256 tiles, one workgroup per CU, up to 256 rows: fewest activation
+//    loads (128 experts of 128 rows, K = 2048: 271 us for both projections
+//    against 288 with 192-row tiles);
+//  - 128 x 128 tiles, two per CU, when the wide tiles are too few to keep HBM
+//    busy: under 192 of them, or under 128 for groups past 64 rows, whose
+//    MFMA work weighs more (16 experts of 27 rows 38.8 -> 31.9 us; 144 wide
+//    tiles of 147 rows 59.6 us against 78.2);
+//  - 192 x 128 tiles, two per CU, past 256 rows, where a group is cut into
+//    chunks anyway (16 groups of 276: 119 -> 81 us).
+bool medium_grouped(const Plan& p, const tl_layout_desc* d, int64_t num_groups, int64_t total_rows,
+                    int64_t max_group_rows, int64_t N, int64_t K, bool swiglu, MediumConfig* cfg, int64_t* grid) {
+    if (max_group_rows <= 16 || total_rows >= (int64_t(1) << 30) || d->tile_m || d->tile_n || d->tile_k) return false;
+    const int64_t kp = p.L.kind == TL_LAYOUT_TILE ? padded_cols(p.L, K) : K;
+    if (256 * kp * 2 >= (int64_t(1) << 32)) return false;   // 32-bit offsets inside a tile's weight rows
+    const int64_t groups = std::min(num_groups, total_rows);
+    const int64_t wide_cols = medium_tile_n(MediumConfig::kWide) / (swiglu ? 2 : 1);
+    const int64_t wide = groups * ((N + wide_cols - 1) / wide_cols);
+    if (max_group_rows > 256) *cfg = MediumConfig::kPair192;
+    else if (wide >= (max_group_rows <= 64 ? 192 : 128)) *cfg = MediumConfig::kWide;
+    else *cfg = MediumConfig::kPair128;
+    // at most total_rows / tile_m whole chunks and one more per group; the
+    // kernel finds each workgroup's group and rows from the device offsets
+    const int64_t cols = medium_tile_n(*cfg) / (swiglu ? 2 : 1);
+    const int64_t slots = total_rows / medium_tile_m(*cfg) + groups;
+    *grid = (slots + 7) / 8 * 8 * ((N + cols - 1) / cols);
+    return *grid < (int64_t(1) << 31);
+}
+
 }  // namespace
 }  // namespace tl
 
@@ -766,6 +823,21 @@ static int grouped_impl(const void* A, int64_t a_rows, const int32_t* token_ids,
     StateRef st;
     rc = get_state(s, 0, &st);
     if (rc != TL_OK) return rc;
+    MediumConfig cfg;
+    int64_t grid = 0;
+    if (medium_grouped(p, layout, num_groups, total_rows, max_group_rows, N, K, swiglu, &cfg, &grid)) {
+        MediumParams m = medium_params(p, A, W, C, N, K, cfg, swiglu);
+        m.fetch = p.count ? st.fetch : nullptr;
+        m.offsets = group_offsets;
+        m.token_ids = token_ids;
+        m.num_groups = num_groups;
+        m.group_stride = group_stride;
+        m.a_rows = int(a_rows);
+        m.total_rows = int(total_rows);
+        m.w_once = max_group_rows <= medium_tile_m(cfg);
+        const bool tile = layout->kind == TL_LAYOUT_TILE;
+        return launch_medium(m, int(grid), cfg, tile, swiglu, s) == hipSuccess ? TL_OK : TL_EHIP;
+    }
     DecodeLaunch d;
     d.A = static_cast<const uint16_t*>(A);
     d.W = static_cast<const uint8_t*>(W);

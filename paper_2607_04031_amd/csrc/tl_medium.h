@@ -1,0 +1,45 @@
+// Row-adaptive GEMM for medium row counts (tl_medium.hip): parameters and
+// configurations.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "tl_internal.h"
+
+namespace tl {
+
+struct MediumParams {
+    const uint16_t* A = nullptr;
+    const uint8_t* W = nullptr;
+    void* C = nullptr;
+    unsigned long long* fetch = nullptr;
+    int N = 0, K = 0;        // N: columns of C (gated launches: I, of 2I weight rows)
+    int64_t strip_bytes = 0;
+    int log2_br = 0, log2_bc = 0, log2_G = 0;
+    int bc_mask = 0;
+    bool out_bf16 = false;
+    bool w_once = false;     // one workgroup reads a weight byte (row chunks do not share it): non-temporal loads
+    int n_tiles = 0;         // column tiles
+    // groups: as tl_gemm_grouped
+    const int* offsets = nullptr;
+    const int* token_ids = nullptr;
+    int num_groups = 0;
+    int64_t group_stride = 0;
+    int a_rows = 0;
+    int total_rows = 0;
+};
+
+// Tiles of C (rows x columns) and what a CU holds of them.
+enum class MediumConfig {
+    kWide,      // 256 x 256, 8 waves, three weight stages, one workgroup per CU
+    kPair192,   // 192 x 128, 4 waves, two weight stages, two workgroups per CU
+    kPair128    // 128 x 128, 4 waves, three weight stages, two workgroups per CU
+};
+inline int medium_tile_m(MediumConfig c) { return c == MediumConfig::kWide ? 256 : c == MediumConfig::kPair192 ? 192 : 128; }
+inline int medium_tile_n(MediumConfig c) { return c == MediumConfig::kWide ? 256 : 128; }
+
+hipError_t launch_medium(const MediumParams& p, int grid, MediumConfig cfg, bool tile, bool swiglu, hipStream_t stream);
+
+}  // namespace tl

@@ -314,3 +314,61 @@ def test_swiglu_graph_replay():
             side.synchronize()
             assert torch.equal(H, eager), f"replay {rep}"
     parity(host_f32(eager), oracle.grouped_swiglu_f64(A, ids, offsets, Ws), "swiglu graph")
+
+
+# Groups past 16 rows take the row-adaptive kernel: row counts at the edges of
+# its 32-row blocks and of its 128-, 192- and 256-row tiles, K below, at and
+# past its 64-wide steps, N around its 128 and 256 columns.  The bound on the
+# largest group (max_rows) and the number of groups select the configuration.
+@pytest.mark.parametrize("kind", [tl.TL_LAYOUT_TILE, tl.TL_LAYOUT_NK_ROW])
+@pytest.mark.parametrize("swiglu", [False, True])
+@pytest.mark.parametrize("counts,N,K,bf16", [
+    ([17, 0, 1, 32], 96, 72, False),
+    ([33, 64, 0, 65], 320, 64, True),
+    ([128, 129, 3], 160, 200, False),
+    ([192, 0, 193, 31], 128, 136, False),
+    ([256, 255, 5], 288, 8, True),
+    ([257, 16, 400], 64, 328, False),
+    ([20] * 70, 800, 128, True),          # two offset rounds of 64 groups, the wide tiles
+    ([90, 0, 20] * 43, 512, 96, False),
+])
+def test_row_adaptive_groups(counts, N, K, bf16, swiglu, kind):
+    """Every row against the oracle; out-of-range ids read zero rows."""
+    import torch
+    E = len(counts)
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    T, a_rows = int(offsets[-1]), 50
+    rng = np.random.default_rng(T + N)
+    ids = rng.integers(0, a_rows, size=T).astype(np.int32)
+    ids[::11], ids[5::13] = -1, a_rows
+    A = synth.normal_bf16((a_rows, K), seed=21)
+    rows_w = 2 * N if swiglu else N
+    distinct = [synth.normal_bf16((rows_w, K), seed=300 + e, sigma=synth.W_SIGMA) for e in range(min(E, 5))]
+    Ws = [distinct[e % len(distinct)] for e in range(E)]
+    tile = kind == tl.TL_LAYOUT_TILE
+    d = tl.layout(kind=kind, G=1024, block_rows=16, out_dtype=tl.TL_OUT_BF16 if bf16 else tl.TL_OUT_F32)
+    stride = tl.tl_tile_bytes(rows_w, K, 2, 1024, 16) if tile else rows_w * K * 2
+    stack = torch.zeros(E * stride // 2, dtype=torch.bfloat16, device="cuda")
+    for e, W in enumerate(Ws):
+        part = stack[e * stride // 2:(e + 1) * stride // 2]
+        if tile:
+            tl.tl_repack(dev_bf16(W), part, rows_w, K, 2, 1024, 16)
+        else:
+            part.copy_(dev_bf16(W).flatten())
+    # bf16 A with one row of zeros for the ids outside [0, a_rows)
+    A0 = np.concatenate([A, np.zeros((1, K), dtype=np.uint16)])
+    ids0 = np.where((ids < 0) | (ids >= a_rows), a_rows, ids)
+    ref = (oracle.grouped_swiglu_f64 if swiglu else oracle.grouped_gemm_f64)(A0, ids0, offsets, Ws)
+    for bound in (max(counts), 2 * max(counts)):
+        C = torch.full((T + 1, N), 7.0, dtype=torch.bfloat16 if bf16 else torch.float32, device="cuda")
+        banner(f"row-adaptive groups {counts[:4]}x{E} N={N} K={K} swiglu={swiglu} kind={kind} bound={bound}")
+        fn = tl.tl_gemm_grouped_swiglu if swiglu else tl.tl_gemm_grouped
+        fetch = tl.TL_FETCH_BLOCK if tile else tl.TL_FETCH_NATIVE
+        fn(dev_bf16(A), a_rows, dev_i32(ids), dev_i32(offsets), E, T, bound, stack, stride, C, N, K, d, fetch)
+        torch.cuda.synchronize()
+        assert bool((C[T] == 7.0).all()), "wrote past the last row"
+        what = f"bound {bound}"
+        if bf16:
+            parity_bf16_out(host_bits(C[:T]), ref, what)
+        else:
+            parity(host_f32(C[:T]), ref, what)
