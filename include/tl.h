@@ -226,7 +226,8 @@ int tl_unpack(const void* src_tm, void* dst, int64_t rows, int64_t cols, int32_t
  * workgroups, or 128x128 tiles; when 256x256 tiles are fewer than the CUs
  * (and K % 64 == 0, N % 256 == 0), every column takes them with K split, up
  * to 8 ways -- at M <= 128, 128x128 tiles with K split when those are fewer
- * than the CUs (N % 128 == 0); see tl_gemm_plan).  layout->elem_bytes = 1 means an FP8 weight (OCP E4M3, one
+ * than the CUs (N % 128 == 0); with M <= 224 in one row of tiles they run on
+ * the row-adaptive kernel; see tl_gemm_plan).  layout->elem_bytes = 1 means an FP8 weight (OCP E4M3, one
  * byte per element, e.g. 64 x 64 memory tiles of 4 KB, Section 3.1): decode
  * kernel only, converted exactly to bf16 in registers (see tl_gemm_w8 for
  * per-channel scales).

@@ -165,9 +165,12 @@ struct Plan {
     bool kn_row = false;         // weight stored [K][N] (N contiguous): the transposing decode kernel
     int split_rest = 0;          // prefill: K splits of the 256 x 256 tiles past n_main (0: 128 x 128 tiles)
     bool persist = false;        // prefill: one workgroup per CU walks the main launch's tiles
+    bool medium = false;         // all rows in one tile of the row-adaptive kernel
+    MediumConfig medium_cfg = MediumConfig::kPair128;
 };
 
 constexpr int kDecodeMaxM = 64;
+constexpr int kMediumMaxM = 224;           // rows of one tile of the row-adaptive kernel
 constexpr int64_t kMaxDim = int64_t(1) << 30;   // largest M, N or K
 constexpr int kTargetWorkgroups = 1024;   // 4 per CU on 256 CUs
 constexpr int kMaxSplitK = 16;            // partials the reduce kernel sums
@@ -484,15 +487,13 @@ int plan_gemm(int64_t M, int64_t N, int64_t K, const tl_layout_desc* d, int32_t 
         // 65 <= M <= 128 (one row of 128-row tiles): 128 x 128 tiles with K
         // split over all the columns in the same way, when they are fewer
         // than the CUs -- no padded rows past 128, against half or more of a
-        // 256-row tile's
+        // 256-row tile's (row-adaptive kernel, see the end of this function)
         if (!d->tile_m && !d->tile_n && M > kDecodeMaxM && M <= 128 && N % 128 == 0 && !p.block_row &&
             (!tile || 128 % p.L.br == 0) && N / 128 < kCUs) {
             const int64_t t128 = N / 128;
             const int64_t S = std::min<int64_t>({kCUs / t128, 8, (K + 63) / 64 / 8});
             if (S >= 2) {
-                p.n_main = 0;                // no main launch: every column splits K
-                p.split_rest = int(S);
-                p.persist = false;
+                p.medium = true;
                 p.pub.tile_m = 128;
                 p.pub.tile_n = 128;
                 p.pub.tile_k = int(p.k_unit);
@@ -510,14 +511,19 @@ int plan_gemm(int64_t M, int64_t N, int64_t K, const tl_layout_desc* d, int32_t 
             if (t256 < kCUs) {
                 const int64_t S = std::min<int64_t>({kCUs / t256, 8, K / 64 / 8});
                 if (S >= 2) {
-                    p.n_main = 0;                // no main launch: every column splits K
-                    p.split_rest = int(S);
+                    if (M <= kMediumMaxM) {
+                        p.medium = true;
+                        p.medium_cfg = MediumConfig::kWide;
+                    } else {
+                        p.n_main = 0;            // no main launch: every column splits K
+                        p.split_rest = int(S);
+                    }
                     p.persist = false;
                     p.pub.tile_m = 256;
                     p.pub.tile_n = 256;
                     p.pub.tile_k = int(p.k_unit);
                     p.pub.split_k = int(S);
-                    p.pub.waves = 4;
+                    p.pub.waves = p.medium ? 8 : 4;
                     p.pub.workgroups = t256 * S;
                     p.pub.workspace_bytes = S * M * N * 4;
                     *P = p;
@@ -581,6 +587,25 @@ int plan_gemm(int64_t M, int64_t N, int64_t K, const tl_layout_desc* d, int32_t 
         // that stays below 2^31 after one more step of 256)
         if (p.pub.workgroups >= (int64_t(1) << 31) || main_tiles >= (int64_t(1) << 31) - kCUs)
             return TL_EUNSUPPORTED;
+        // M <= kMediumMaxM, no tile requested, all rows in one tile: the
+        // row-adaptive kernel (tl_medium.hip), which computes only the 32-row
+        // blocks that exist and streams the weight two K steps ahead, on the
+        // same tiles and K splits.  128 x 128 tiles against prefill_kernel,
+        // Llama-70B shapes, bf16 out, one box, M = 65 / 96 / 128: QKV (S = 3)
+        // 43.5 / 45.5 / 46.9 -> 36.8 / 38.6 / 42.4 us, O 34.9 / 36.8 / 38.7 ->
+        // 31.0 / 32.8 / 36.6, gate+up (S = 1) 177 / 185 / 193 -> 147 / 161 /
+        // 177, down 109 / 112 / 115 -> 84 / 88 / 100.  256 x 256 tiles against
+        // prefill_w4_kernel, M = 129 / 192 / 224 / 256: gate+up 213 / 223 /
+        // 231 / 243 -> 176 / 205 / 227 / 248, QKV (S = 6) 56.9 / 60.0 / 63.3 /
+        // 63.5 -> 44.8 / 51.7 / 56.9 / 61.5: even at 256 rows, where a full
+        // tile is MFMA work that the four-wave kernel does with fewer LDS reads.
+        if (!d->tile_m && !d->tile_n && M <= kMediumMaxM && !p.block_row && !p.split_rest &&
+            mt == 1 && p.n_main == N) {
+            p.medium = true;
+            p.medium_cfg = tn == 256 ? MediumConfig::kWide : MediumConfig::kPair128;
+            p.persist = false;
+            p.pub.waves = tn == 256 ? 8 : 4;
+        }
         // split_k reports the K splits of the remaining columns' tiles
         p.pub.split_k = p.split_rest ? p.split_rest : 1;
         p.pub.workspace_bytes = p.split_rest ? int64_t(p.split_rest) * M * (N - p.n_main) * 4 : 0;
@@ -735,7 +760,24 @@ static int gemm_impl(const void* A, const void* W, const float* scales, void* C,
     }
 
     hipError_t e;
-    if (p.pub.kernel == 1) {
+    if (p.medium) {
+        MediumParams m = medium_params(p, A, W, C, N, K, p.medium_cfg, false);
+        m.fetch = p.count ? st.fetch : nullptr;
+        m.total_rows = int(M);
+        m.split_k = p.pub.split_k;
+        m.ws = st.ws;
+        m.ws_stride = (M * N + 3) / 4 * 4;
+        m.w_once = true;
+        e = launch_medium(m, int(p.pub.workgroups), p.medium_cfg, layout->kind == TL_LAYOUT_TILE, false, s);
+        DecodeLaunch r;
+        r.C = C;
+        r.ws = st.ws;
+        r.M = M;
+        r.N = N;
+        r.split_k = p.pub.split_k;
+        r.out_bf16 = p.out_bf16;
+        e = launch_splitk_reduce(r, e, s);
+    } else if (p.pub.kernel == 1) {
         DecodeLaunch d;
         d.A = static_cast<const uint16_t*>(A);
         d.W = static_cast<const uint8_t*>(W);

@@ -22,6 +22,11 @@ struct MediumParams {
     bool out_bf16 = false;
     bool w_once = false;     // one workgroup reads a weight byte (row chunks do not share it): non-temporal loads
     int n_tiles = 0;         // column tiles
+    // one weight (num_groups 0): total_rows rows in one tile, K split split_k
+    // ways (> 1: fp32 partials at ws, ws_stride floats apart)
+    int split_k = 1;
+    float* ws = nullptr;
+    int64_t ws_stride = 0;
     // groups: as tl_gemm_grouped
     const int* offsets = nullptr;
     const int* token_ids = nullptr;

@@ -1,7 +1,9 @@
 // Row-adaptive GEMM for medium row counts: C = A * W^T with bf16 MFMA 32x32x16
 // and fp32 accumulation, W tile-major (or row-major [N][K]), for stacks of
 // weights that each serve some tens to some hundreds of rows (the expert
-// GEMMs of a mixture-of-experts layer over a prompt or a large decode batch).
+// GEMMs of a mixture-of-experts layer over a prompt or a large decode batch)
+// and for one weight at up to 224 rows (K split across workgroups where its
+// tiles are fewer than the CUs, fp32 partials summed in split order).
 //
 // Between decode (16 rows or fewer: read the weights, the rest is free) and
 // prefill (MFMA-bound) a call is bound by streaming each weight byte once
@@ -21,6 +23,9 @@
 //  - lanes without a row, or past K, load from a 16-byte zero chunk, so
 //    ragged rows, out-of-range token ids and a partial last K step need no
 //    masks in the loop.
+// Llama-70B gate+up, one MI355X, bf16 out, M = 65 / 96 / 128 / 192: 147 / 161 /
+// 177 / 205 us (177 / 185 / 193 / 223 on the kernels of tl_prefill.hip; the
+// weight's read takes 132); the planner's comments have the other shapes.
 // Qwen-3-30B-A3B experts, one MI355X, both projections, bf16 out: 512 / 1024 /
 // 2048 tokens (32 / 64 / 128 rows per expert) 379 / 589 / 1001 us on the
 // decode kernel's 64-row passes -> 213 / 230 / 271 us; reading the weights
@@ -83,7 +88,7 @@ __device__ inline void lds_load16_at(const uint8_t* ptr, uint8_t* lds) {
 
 #define TL_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (((n) >> 4) << 14) | 0x0F70)
 
-template <int WN, int MAXB, int WST, bool TILE, bool SWIGLU>
+template <int WN, int MAXB, int WST, bool TILE, bool GROUPED, bool SWIGLU>
 __global__ __launch_bounds__(128 * WN) __attribute__((amdgpu_waves_per_eu(2, 2))) void medium_kernel(MediumParams p) {
     constexpr int NWAVES = 2 * WN;
     constexpr int BN = 64 * WN;                  // weight rows per tile
@@ -103,9 +108,9 @@ __global__ __launch_bounds__(128 * WN) __attribute__((amdgpu_waves_per_eu(2, 2))
     const int half = wave / WN, nq = wave % WN;
 
     // ---- which rows and columns ----
-    int nt, row0, rows;                          // output rows [row0, row0 + rows)
+    int nt, split = 0, row0, rows;               // output rows [row0, row0 + rows)
     const uint8_t* W = p.W;
-    {
+    if constexpr (GROUPED) {
         // workgroup u runs on XCD u mod 8; the tiles of one slot stay on one
         // XCD (they share rows of A) and the slots in use, a prefix of all
         // slots, are dealt to the XCDs in turn
@@ -149,15 +154,27 @@ __global__ __launch_bounds__(128 * WN) __attribute__((amdgpu_waves_per_eu(2, 2))
         row0 = r0 + b0 * 32;
         rows = min(r0 + b1 * 32, r1) - row0;
         W += int64_t(group) * p.group_stride;
+    } else {
+        // one weight, all rows in one tile: column tiles, then K splits; each
+        // XCD takes a contiguous range (its workgroups share a K range of A)
+        const int T = gridDim.x, b = blockIdx.x;
+        const int lb = (T % 8 == 0) ? (b % 8) * (T / 8) + b / 8 : b;
+        split = lb / p.n_tiles;
+        nt = lb - split * p.n_tiles;
+        row0 = 0;
+        rows = p.total_rows;
     }
-    const int KT = (p.K + 63) / 64;
+    // this workgroup's 64-wide K steps: [kt0, kt0 + KT)
+    const int ksteps = (p.K + 63) / 64;
+    const int kt0 = GROUPED ? 0 : int(int64_t(ksteps) * split / p.split_k);
+    const int KT = GROUPED ? ksteps : int(int64_t(ksteps) * (split + 1) / p.split_k) - kt0;
     const int nblocks = (rows + 31) / 32;
 
     // ---- per-lane sources ----
     const int lrow = lane >> 3, lpos = lane & 7;
     const uint8_t* Ab = reinterpret_cast<const uint8_t*>(p.A);
     const uint8_t* zero = reinterpret_cast<const uint8_t*>(&g_zero_chunk);
-    const uint8_t* aptr[AI];                     // this lane's chunk of the next A step
+    const uint8_t* aptr[AI];                     // this lane's chunk of the first A step
     uint32_t astep[AI];                          // 128, or 0 where there is no row
     int achunk[AI];                              // k of the chunk inside a step
 #pragma unroll
@@ -166,12 +183,14 @@ __global__ __launch_bounds__(128 * WN) __attribute__((amdgpu_waves_per_eu(2, 2))
         const int c = lpos ^ ((r >> 1) & 7);
         bool ok = r < rows;
         int src = row0 + r;
-        if (p.token_ids) {
-            if (ok) src = p.token_ids[src];
-            ok = ok && src >= 0 && src < p.a_rows;
+        if constexpr (GROUPED) {
+            if (p.token_ids) {
+                if (ok) src = p.token_ids[src];
+                ok = ok && src >= 0 && src < p.a_rows;
+            }
         }
         achunk[i] = c * 8;
-        aptr[i] = ok ? Ab + (int64_t(src) * p.K + c * 8) * 2 : zero;
+        aptr[i] = ok ? Ab + (int64_t(src) * p.K + int64_t(kt0) * 64 + c * 8) * 2 : zero;
         astep[i] = ok ? 128u : 0u;
     }
     auto w_koff = [&](int k) -> uint32_t {
@@ -204,7 +223,7 @@ __global__ __launch_bounds__(128 * WN) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
     auto issue_a = [&](int s) {
         uint8_t* st = smem + (s & 1) * A_ST;
-        const int left = p.K - s * 64;           // columns of the step inside K
+        const int left = p.K - (kt0 + s) * 64;           // columns of the step inside K
 #pragma unroll
         for (int i = 0; i < AI; ++i) {
             const int ga = wave + NWAVES * i;
@@ -216,7 +235,7 @@ __global__ __launch_bounds__(128 * WN) __attribute__((amdgpu_waves_per_eu(2, 2))
     };
     auto issue_w = [&](int s) {
         uint8_t* st = smem + 2 * A_ST + (WST == 3 ? s % 3 : (s & 1)) * W_ST;
-        const int k0 = s * 64;
+        const int k0 = (kt0 + s) * 64;
         const uint8_t* wk = wtile + w_koff(k0);
         if (k0 + 64 <= p.K && p.w_once) {        // uniform
 #pragma unroll
@@ -312,7 +331,9 @@ __global__ __launch_bounds__(128 * WN) __attribute__((amdgpu_waves_per_eu(2, 2))
     uint8_t* E = smem + wave * 32 * ESTRIDE;
     constexpr int CW = SWIGLU ? 32 : 64;         // output columns per wave
     const int col0 = n_base + nq * CW;
-    float* F = static_cast<float*>(p.C);
+    // one K range of several: its fp32 partial, summed by the split-K reduce
+    const bool part = !GROUPED && p.split_k > 1;
+    float* F = part ? p.ws + int64_t(split) * p.ws_stride : static_cast<float*>(p.C);
     uint16_t* H = static_cast<uint16_t*>(p.C);
 #pragma unroll
     for (int i = 0; i < MAXB; ++i) {
@@ -340,7 +361,7 @@ __global__ __launch_bounds__(128 * WN) __attribute__((amdgpu_waves_per_eu(2, 2))
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
         const int rb = (half + 2 * i) * 32;      // first row of the block in the tile
-        if (p.out_bf16) {
+        if (p.out_bf16 && !part) {
             constexpr int LPR = CW / 8;          // lanes per row, eight columns each
 #pragma unroll
             for (int q = 0; q < 32 * LPR / 64; ++q) {
@@ -389,12 +410,15 @@ __global__ __launch_bounds__(128 * WN) __attribute__((amdgpu_waves_per_eu(2, 2))
 template <int WN, int MAXB, int WST>
 hipError_t launch_c(const MediumParams& p, int grid, bool tile, bool swiglu, hipStream_t stream) {
     const dim3 g(grid), b(128 * WN);
-    if (swiglu) {
-        if (tile) hipLaunchKernelGGL((medium_kernel<WN, MAXB, WST, true, true>), g, b, 0, stream, p);
-        else hipLaunchKernelGGL((medium_kernel<WN, MAXB, WST, false, true>), g, b, 0, stream, p);
+    if (p.num_groups == 0) {
+        if (tile) hipLaunchKernelGGL((medium_kernel<WN, MAXB, WST, true, false, false>), g, b, 0, stream, p);
+        else hipLaunchKernelGGL((medium_kernel<WN, MAXB, WST, false, false, false>), g, b, 0, stream, p);
+    } else if (swiglu) {
+        if (tile) hipLaunchKernelGGL((medium_kernel<WN, MAXB, WST, true, true, true>), g, b, 0, stream, p);
+        else hipLaunchKernelGGL((medium_kernel<WN, MAXB, WST, false, true, true>), g, b, 0, stream, p);
     } else {
-        if (tile) hipLaunchKernelGGL((medium_kernel<WN, MAXB, WST, true, false>), g, b, 0, stream, p);
-        else hipLaunchKernelGGL((medium_kernel<WN, MAXB, WST, false, false>), g, b, 0, stream, p);
+        if (tile) hipLaunchKernelGGL((medium_kernel<WN, MAXB, WST, true, true, false>), g, b, 0, stream, p);
+        else hipLaunchKernelGGL((medium_kernel<WN, MAXB, WST, false, true, false>), g, b, 0, stream, p);
     }
     return hipGetLastError();
 }

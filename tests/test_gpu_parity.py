@@ -912,3 +912,25 @@ def test_moe_attention_stacked_qkv():
     tl.tl_gemm(dev_bf16(A), cat, C, M, stacked.shape[0], K, tl.layout(), tl.TL_FETCH_BLOCK)
     _sync()
     parity(host_f32(C), oracle.gemm_f64(A, stacked), "stacked qkv")
+
+
+# The row-adaptive kernel on one weight: rows at the edges of its 32-row blocks
+# and its two tiles, and one row past where the plan leaves it; K splits and
+# none, a ragged N, a partial last K step, a row-major weight.
+@pytest.mark.parametrize("M,N,K,row_major", [
+    (65, 1000, 520, False), (96, 384, 1096, True), (97, 4096, 1024, False), (127, 130, 72, False), (128, 1, 8, True),
+    (129, 512, 1024, False), (160, 2048, 1024, True), (161, 32768, 128, False), (192, 33024, 64, False),
+    (193, 32768, 192, True), (224, 1024, 2048, False), (225, 1024, 2048, False), (48, 32768, 200, False),
+])
+def test_row_adaptive_edges(M, N, K, row_major):
+    kind = tl.TL_LAYOUT_NK_ROW if row_major else tl.TL_LAYOUT_TILE
+    fetch = tl.TL_FETCH_NATIVE if row_major else tl.TL_FETCH_BLOCK
+    d = tl.layout(kind=kind, G=1024, block_rows=16)
+    banner(f"row-adaptive edges M={M} N={N} K={K} row_major={row_major} plan={tl.tl_gemm_plan(M, N, K, d, fetch)}")
+    A = synth.normal_bf16((M, K), seed=180 + M)
+    W = synth.normal_bf16((N, K), seed=181, sigma=synth.W_SIGMA)
+    y_ref = oracle.gemm_f64(A, W)
+    Wd = dev_bf16(W) if row_major else tl.repack(dev_bf16(W), 1024, 16)
+    parity(host_f32(tl.gemm(dev_bf16(A), Wd, N, d, fetch)), y_ref, "f32")
+    db = tl.layout(kind=kind, G=1024, block_rows=16, out_dtype=tl.TL_OUT_BF16)
+    parity_bf16_out(host_bits(tl.gemm(dev_bf16(A), Wd, N, db, fetch)), y_ref, "bf16")
