@@ -378,15 +378,16 @@ int plan_gemm(int64_t M, int64_t N, int64_t K, const tl_layout_desc* d, int32_t 
         if (waves == 16 && mn > 1) waves = 8;
         if (waves == 8 && mn > 4 && !(mn == 8 && !p.fp8 && !p.block_row)) waves = 4;
         p.waves = waves;
-        // 17 <= M <= 32 on whole tile-major strips: stage the activations in
-        // LDS, one 8-wave workgroup per CU taking T of the 32-row tiles and
-        // one of S K ranges, when the (T, S) grid covers the CUs in whole
-        // rounds (A crosses L2 -> CU once per T tiles instead of once per
-        // tile) -- unless its K ranges are short (under 8 chunks, so its
-        // staging and wave reduction weigh more) while the streaming plan
-        // already has one or two workgroups per CU (Llama O at M = 32:
-        // 29.8 vs 29.0 us; QKV, whose streaming plan needs 1120 workgroups,
-        // 35.6 vs 43.0; down 81.7 vs 84.1; gate+up 150.9 vs 181.4)
+        // 17 <= M <= 32 on whole tile-major strips: weights and activations
+        // through LDS (tl_decode_lds.hip), one 8-wave workgroup per CU taking
+        // T of the 32-row tiles and one of S K ranges, when the (T, S) grid
+        // covers the CUs in whole rounds (A crosses L2 -> CU once per T tiles
+        // instead of once per tile) -- unless its K ranges are short (under
+        // 2048 columns, so its start and wave reduction weigh more) while the
+        // streaming plan already has one or two workgroups per CU (Llama O at
+        // M = 32: 28.7 us streaming).  QKV at M = 32, whose streaming plan
+        // needs 1120 workgroups, 43.0 -> 31.5 us, down 84.1 -> 72.1, gate+up
+        // 181 -> 137
         if (tile && !p.fp8 && p.m_tiles16 == 2 && !d->tile_n && !d->split_k && N % 32 == 0 && K % 512 == 0 &&
             p.L.br <= 32 && 512 % p.k_unit == 0) {
             const int64_t strips = N / 32, chunks = K / 512;
@@ -410,14 +411,14 @@ int plan_gemm(int64_t M, int64_t N, int64_t K, const tl_layout_desc* d, int32_t 
             }
         }
         // 33 <= M <= 64 (four M tiles) on whole tile-major strips: the same
-        // staging with T = 4 tiles per workgroup (64 KB chunks of A; at T = 5
-        // the registers spill) and the largest S (K ranges of >= 4 chunks)
-        // whose grid fits one round of the CUs, when that fills at least 7/8
-        // of it (or S = 1 when the tile groups fill a round by themselves):
-        // a 64-row streaming tile reloads as many activation bytes from L2 as
-        // it streams weight bytes (Llama shapes, bf16 out, one box, M = 33 /
-        // 48 / 64: QKV (S = 3, 240 workgroups) 50 / 54 / 58 -> 41 / 42 / 44 us,
-        // O 33 / 35 / 39 -> 32 / 33 / 35, down 93 / 100 / 112 -> 88 / 90 / 92)
+        // with T = 4 tiles per workgroup and the largest S (K ranges of >= 2048
+        // columns) whose grid fits one round of the CUs, when that fills at
+        // least 7/8 of it (or S = 1 when the tile groups fill a round by
+        // themselves): a 64-row streaming tile reloads as many activation
+        // bytes from L2 as it streams weight bytes (Llama shapes, bf16 out,
+        // one box, M = 33 / 48 / 64: QKV (S = 3, 240 workgroups) 50 / 54 / 58
+        // -> 32 / 32 / 33 us, O 33 / 35 / 39 -> 29 / 30 / 32, down 93 / 100 /
+        // 112 -> 73 / 73 / 74)
         if (tile && !p.fp8 && p.m_tiles16 == 4 && !d->tile_n && !d->split_k && N % 128 == 0 && K % 512 == 0 &&
             p.L.br <= 32 && 512 % p.k_unit == 0) {
             const int64_t groups = N / 128, chunks = K / 512;
