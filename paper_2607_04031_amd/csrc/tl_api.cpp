@@ -176,6 +176,27 @@ constexpr int kTargetWorkgroups = 1024;   // 4 per CU on 256 CUs
 constexpr int kMaxSplitK = 16;            // partials the reduce kernel sums
 constexpr int kCUs = 256;                  // MI355X compute units
 
+// Estimated time (us) of prefill_w4_kernel with tile_m x 256 tiles and K split
+// S ways, 0 where that is no plan: the larger of the padded rows' MFMA work at
+// the rate the whole chip sustains (1.43 PFLOP/s: its clock falls under that
+// load) and the rounds of workgroups at the rate of a lightly loaded CU (0.86 /
+// 1.1 / 1.36 us per 64-wide K step at 192 / 256 / 320 rows); half of the
+// weight's read (6.5 TB/s), which MFMA work of under 1000 rows hides only in
+// part; and the fp32 partials, written and read at 5 TB/s, with the reduce's
+// launch.  Fitted to the Llama-70B shapes at M = 256 - 1500 (within 10 %).
+// M = 300 / 384, 256-row tiles -> the choice, us: gate+up 408 / 408 -> 283 /
+// 330 (320 / 192 rows), down 209 / 211 -> 170 / 174 (320 x 6 / 192 x 4), QKV
+// 87 / 90 -> 74 / 74, O 75 / 77 -> 61 / 63; at 512 and 1024 rows 256 stays.
+double w4_estimate_us(int64_t M, int64_t N, int64_t K, int tile_m, int64_t S) {
+    const int64_t mt = (M + tile_m - 1) / tile_m, tiles = mt * (N / 256), steps = K / 64;
+    if (S > 1 && (tiles * S > kCUs || steps / S < 8 || S * M * N * 4 > kScratchBytes)) return 0;
+    const double step_us = tile_m == 192 ? 0.86 : tile_m == 256 ? 1.1 : 1.36;
+    const double mfma = 2.0 * double(mt * tile_m) * double(N) * double(K) / 1.43e9;
+    const double rounds = double((tiles * S + kCUs - 1) / kCUs) * double((steps + S - 1) / S) * step_us;
+    const double partials = S > 1 ? 2.0 * double(S * M * N * 4) / 5e6 + 4.0 : 0.0;
+    return std::max(mfma, rounds) + 0.5 * double(N * K * 2) / 6.5e6 + partials;
+}
+
 int plan_gemm(int64_t M, int64_t N, int64_t K, const tl_layout_desc* d, int32_t fetch_mode,
               Plan* P) {
     if (!d) return TL_EINVAL;
@@ -502,6 +523,47 @@ int plan_gemm(int64_t M, int64_t N, int64_t K, const tl_layout_desc* d, int32_t 
                 p.pub.waves = 4;
                 p.pub.workgroups = t128 * S;
                 p.pub.workspace_bytes = S * M * N * 4;
+                *P = p;
+                return TL_OK;
+            }
+        }
+        // 192- or 320-row tiles (K split S ways, or not) where they are clearly
+        // faster than 256-row ones by the estimate above; past 1024 rows only
+        // where 256-row tiles fit one round of the CUs (more of them are cut
+        // into whole rounds and a remainder below, which it does not model)
+        if (!d->tile_m && !d->tile_n && M > kMediumMaxM && M % 256 != 0 && K % 64 == 0 && N % 256 == 0 &&
+            !p.block_row && (!tile || 256 % p.L.br == 0) && (M < 1024 || (M + 255) / 256 * (N / 256) <= kCUs)) {
+            int best_tm = 256, best_s = 1;
+            double best = 0;
+            // (256-row tiles too few for a K split of 8 steps and for half the
+            // CUs run as 128 x 128 tiles below, which stay)
+            const int64_t t256 = (M + 255) / 256 * (N / 256);
+            if (M >= 1024 || 2 * t256 >= kCUs || K / 64 >= 16)
+                for (int64_t S = 1; S <= 8; ++S) {
+                    const double c = w4_estimate_us(M, N, K, 256, S);
+                    if (c > 0 && (best == 0 || c < best)) best = c;
+                }
+            best *= 0.9;
+            for (int c_tm : {192, 320})
+                for (int64_t S = 1; S <= 8; ++S) {
+                    const double c = w4_estimate_us(M, N, K, c_tm, S);
+                    if (c > 0 && c < best) {
+                        best = c;
+                        best_tm = c_tm;
+                        best_s = int(S);
+                    }
+                }
+            const int64_t tiles = (M + best_tm - 1) / best_tm * (N / 256);
+            if (best_tm != 256 && tiles * best_s < (int64_t(1) << 31)) {
+                p.n_main = best_s > 1 ? 0 : N;   // K split: no main launch
+                p.split_rest = best_s > 1 ? best_s : 0;
+                p.pub.tile_m = best_tm;
+                p.pub.tile_n = 256;
+                p.pub.tile_k = int(p.k_unit);
+                p.pub.split_k = best_s;
+                p.pub.waves = 4;
+                p.pub.workgroups = tiles * best_s;
+                p.pub.workspace_bytes = best_s > 1 ? best_s * M * N * 4 : 0;
                 *P = p;
                 return TL_OK;
             }

@@ -341,24 +341,38 @@ __device__ inline void load_lds16(const uint8_t* base, uint32_t voff, uint8_t* l
 // VGPRs; persistent bf16 only, whose epilogue needs no LDS).  A 256 x 320
 // tile fills the CUs in whole rounds where 256 x 256 does not (QKV at
 // M = 2048: 256 tiles instead of 320).
-template <bool TILE, bool OUT_BF16, bool PERSIST = false, int NJ = 4>
+//
+// MI: 32-row MFMA tiles per wave along M -- 4, or 3 or 5 (192 x 256 and
+// 320 x 256 tiles, outside the persistent grid) for row counts that 256-row
+// tiles would pad: the whole chip's rate under MFMA load is bounded by its
+// clock, so padded rows cost their full share.  M = 300, bf16 out, one
+// MI355X: gate+up 408 us on 2 x 224 tiles of 256 rows -> 283 on 224 of 320,
+// the Llama-70B layer 784 -> 600 us; per 64-wide K step of a lightly loaded
+// CU 0.86 / 1.1 / 1.36 us at 192 / 256 / 320 rows.
+template <bool TILE, bool OUT_BF16, bool PERSIST = false, int NJ = 4, int MI = 4>
 __global__ __launch_bounds__(256) void prefill_w4_kernel(PrefillParams p) {
     static_assert(!PERSIST || OUT_BF16, "the persistent grid writes bf16");
     static_assert(NJ == 4 || (NJ == 5 && PERSIST), "256 x 320 tiles: persistent bf16 only");
-    constexpr int BM = 256, BN = 64 * NJ, BK = 64;
-    constexpr int HALF = BM * BK * 2;            // A tile of a step: 32 KB
+    static_assert(MI == 4 || ((MI == 3 || MI == 5) && NJ == 4 && !PERSIST), "192- and 320-row tiles: 256 columns");
+    constexpr int BM = 64 * MI, BN = 64 * NJ, BK = 64;
+    constexpr int HALF = BM * BK * 2;            // A tile of a step: 32 KB (24 and 40 KB at 192 and 320 rows)
     constexpr int WHALF = BN * BK * 2;           // W tile of a step: 32 or 40 KB
     // LDS: two A stages, then WST weight stages -- three for 256 x 256 tiles
     // (step s + 2's weight tile loads during step s, so its latency has two
-    // steps to hide in), two for 256 x 320 (the LDS budget)
-    constexpr int WST = NJ == 4 ? 3 : 2;
+    // steps to hide in), two for 256 x 320 and 320 x 256 (the LDS budget)
+    constexpr int WST = NJ == 4 && MI <= 4 ? 3 : 2;
     constexpr int LDS_OPS = 2 * HALF + WST * WHALF;
     constexpr int WROWS = BN / 4;                // W rows each wave loads per step
     constexpr int NWL = WROWS / 8;               // ... in loads of 8 rows: 8 or 10
-    constexpr int NLOAD = 8 + NWL;               // loads per step and wave
-    constexpr int NREAD = 4 + NJ;                // fragment reads per sub-step
+    constexpr int AROWS = BM / 4;                // A rows each wave loads per step
+    constexpr int NAL = AROWS / 8;               // ... in loads of 8 rows
+    constexpr int NLOAD = NAL + NWL;             // loads per step and wave
+    constexpr int NREAD = MI + NJ;               // fragment reads per sub-step
+    // bf16 C straight from registers: a persistent grid, and 320 rows (whose
+    // C tile does not fit in LDS)
+    constexpr bool DIRECT = PERSIST || MI == 5;
     constexpr int C_STAGE = BM * 576;            // bf16 epilogue: the C tile with 576-byte rows
-    constexpr int LDS_BYTES = (OUT_BF16 && !PERSIST && C_STAGE > LDS_OPS) ? C_STAGE : LDS_OPS;
+    constexpr int LDS_BYTES = (OUT_BF16 && !DIRECT && C_STAGE > LDS_OPS) ? C_STAGE : LDS_OPS;
     static_assert(LDS_BYTES <= 160 * 1024, "LDS budget");
     __shared__ __attribute__((aligned(16))) uint8_t smem[LDS_BYTES];
 
@@ -389,12 +403,12 @@ __global__ __launch_bounds__(256) void prefill_w4_kernel(PrefillParams p) {
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wm = wave >> 1, wn = wave & 1;
 
-    // loads: wave w writes rows 64 w .. 64 w + 63 of the A tile and rows
+    // loads: wave w writes rows AROWS w .. of the A tile and rows
     // WROWS w .. WROWS (w + 1) - 1 of the W tile, in instructions of 8 rows;
     // lane l: row + l / 8, LDS position l % 8
     const int lrow = lane >> 3, lpos = lane & 7;
     const uint8_t* Ab = reinterpret_cast<const uint8_t*>(p.A);
-    uint32_t a_off[8], w_row[NWL];
+    uint32_t a_off[NAL], w_row[NWL];
     // Eq. 1's byte offset of column k inside a strip (row-major: 2 k).  For a
     // step start k0 (a multiple of 64) and a chunk start 8 c < 64 it splits,
     // w_koff(k0 + 8 c) = w_koff(k0) + w_koff(8 c): a memory tile at least 64
@@ -409,8 +423,8 @@ __global__ __launch_bounds__(256) void prefill_w4_kernel(PrefillParams p) {
     // uniform base, so a load needs no vector arithmetic)
     auto set_a_rows = [&](int um0) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int r = 64 * wave + 8 * i + lrow;
+        for (int i = 0; i < NAL; ++i) {
+            const int r = AROWS * wave + 8 * i + lrow;
             const int c = lpos ^ ((r >> 1) & 7);
             const uint32_t m = uint32_t(min(um0 + r, p.M - 1));
             a_off[i] = (m * uint32_t(p.K) + uint32_t(c * 8)) * 2u;
@@ -438,21 +452,21 @@ __global__ __launch_bounds__(256) void prefill_w4_kernel(PrefillParams p) {
     auto w_stage = [&](int g, int s) -> uint8_t* {
         return smem + 2 * HALF + (WST == 3 ? (g + s) % 3 : (s & 1)) * WHALF;
     };
-    // load q (0 .. NLOAD - 1) of step s: q < 8 the A rows 8 q .. of this
-    // wave's 64-row share, q >= 8 the W rows 8 (q - 8) .. of its WROWS-row share
+    // load q (0 .. NLOAD - 1) of step s: q < NAL the A rows 8 q .. of this
+    // wave's share, q >= NAL the W rows 8 (q - NAL) .. of its share
     auto issue_one = [&](int s, int q) {
         const int k0 = (kt0 + s) * BK;
-        if (q < 8) load_lds16(Ab + size_t(k0) * 2, a_off[q], smem + (s & 1) * HALF + wave * 8192 + q * 1024);
-        else load_lds16(p.W + w_koff(k0), w_row[q - 8], w_stage(g_ld, s) + wave * (WROWS * 128) + (q - 8) * 1024);
+        if (q < NAL) load_lds16(Ab + size_t(k0) * 2, a_off[q], smem + (s & 1) * HALF + wave * (AROWS * 128) + q * 1024);
+        else load_lds16(p.W + w_koff(k0), w_row[q - NAL], w_stage(g_ld, s) + wave * (WROWS * 128) + (q - NAL) * 1024);
     };
     // fragments: lane reads row lane % 32 of its 32-row tile at K chunk
     // 2 * sub-step + lane / 32; offsets of sub-step 0 (a sub-step adds 2
     // chunks, XORed into the position)
-    int fa_row[4], fb_row[NJ];
-    int fa_sw[4], fb_sw[NJ];
+    int fa_row[MI], fb_row[NJ];
+    int fa_sw[MI], fb_sw[NJ];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int ra = wm * 128 + i * 32 + (lane & 31);
+    for (int i = 0; i < MI; ++i) {
+        const int ra = wm * (32 * MI) + i * 32 + (lane & 31);
         fa_row[i] = ra * 128;
         fa_sw[i] = (ra >> 1) & 7;
     }
@@ -466,15 +480,15 @@ __global__ __launch_bounds__(256) void prefill_w4_kernel(PrefillParams p) {
     // fragment q (0 .. NREAD - 1) of sub-step ss of step s: q < NJ W tile q,
     // else A tile q - NJ (the next sub-step's first MFMAs take A tile 0 with
     // every W tile, so the W tiles are read first)
-    auto fread_one = [&](int s, int ss, int q, bf16x8 (&fa)[4], bf16x8 (&fb)[NJ]) {
+    auto fread_one = [&](int s, int ss, int q, bf16x8 (&fa)[MI], bf16x8 (&fb)[NJ]) {
         const int c = 2 * ss + khalf;
         if (q < NJ) fb[q] = *reinterpret_cast<const bf16x8*>(w_stage(g_rd, s) + fb_row[q] + ((c ^ fb_sw[q]) << 4));
         else fa[q - NJ] = *reinterpret_cast<const bf16x8*>(smem + (s & 1) * HALF + fa_row[q - NJ] + ((c ^ fa_sw[q - NJ]) << 4));
     };
-    f32x16 acc[4][NJ];
+    f32x16 acc[MI][NJ];
     auto zero_acc = [&]() {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < MI; ++i)
 #pragma unroll
             for (int j = 0; j < NJ; ++j)
 #pragma unroll
@@ -487,38 +501,43 @@ __global__ __launch_bounds__(256) void prefill_w4_kernel(PrefillParams p) {
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
     };
-    bf16x8 fa0[4], fb0[NJ], fa1[4], fb1[NJ];
-    // one sub-step: 4 NJ MFMAs on (fa, fb); after MFMA q, fragment q / 2 of
+    bf16x8 fa0[MI], fb0[NJ], fa1[MI], fb1[NJ];
+    // one sub-step: MI NJ MFMAs on (fa, fb); after MFMA q, fragment q / 2 of
     // sub-step rss of step rs into (ga, gb) when q is even (READ, the first
-    // NREAD) and load q / 2 + lq0 of step ls when q is odd (LOAD: the eight
-    // A loads from lq0 = 0 or the NWL W loads from lq0 = 8).  READ, LOAD and
-    // lq0 are compile-time at every call, so the loop holds no branch
-    // between its MFMAs.
-    auto substep = [&](auto read_c, auto load_c, const bf16x8 (&fa)[4], const bf16x8 (&fb)[NJ], int rs, int rss,
-                       bf16x8 (&ga)[4], bf16x8 (&gb)[NJ], int ls, int lq0) {
+    // NREAD) and load q / 2 + lq0 of step ls when q is odd (LOAD: the NAL
+    // A loads from lq0 = 0 or the NWL W loads from lq0 = NAL).  With 12 MFMAs
+    // (MI = 3) the last slots take the seventh read and the seventh and
+    // eighth load as well.  READ, LOAD and lq0 are compile-time at every
+    // call, so the loop holds no branch between its MFMAs.
+    constexpr int SLOTS = MI * NJ;
+    auto substep = [&](auto read_c, auto load_c, const bf16x8 (&fa)[MI], const bf16x8 (&fb)[NJ], int rs, int rss,
+                       bf16x8 (&ga)[MI], bf16x8 (&gb)[NJ], int ls, int lq0) {
         constexpr bool READ = decltype(read_c)::value, LOAD = decltype(load_c)::value;
 #pragma unroll
-        for (int q = 0; q < 4 * NJ; ++q) {
-            if (q % NJ < 4) {
+        for (int q = 0; q < SLOTS; ++q) {
+            if (q % NJ < 4 && q / NJ < 4) {
                 acc[q / NJ][q % NJ] =
                     __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[q / NJ], fb[q % NJ], acc[q / NJ][q % NJ], 0, 0, 0);
             } else {
-                // the fifth column of tiles keeps its sums in VGPRs (the
-                // first four fill the 256 AGPRs; the compiler does not split
-                // the accumulators between the two files by itself).  Its
-                // previous MFMA on the same sums is 4 NJ - 1 MFMAs back, far
-                // beyond any dependency wait.
+                // the fifth column (or row) of tiles keeps its sums in VGPRs
+                // (the first four fill the 256 AGPRs; the compiler does not
+                // split the accumulators between the two files by itself).
+                // Its previous MFMA on the same sums is SLOTS - 1 MFMAs back,
+                // far beyond any dependency wait.
                 asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0"
-                             : "+v"(acc[q / NJ][4])
-                             : "v"(fa[q / NJ]), "v"(fb[4]));
+                             : "+v"(acc[q / NJ][q % NJ])
+                             : "v"(fa[q / NJ]), "v"(fb[q % NJ]));
             }
             if ((q & 1) == 0) {
                 if constexpr (READ) {
                     if ((q >> 1) < NREAD) fread_one(rs, rss, q >> 1, ga, gb);
+                    if (q == SLOTS - 2 && SLOTS / 2 < NREAD) fread_one(rs, rss, NREAD - 1, ga, gb);
                 }
             } else {
                 if constexpr (LOAD) {
-                    if ((q >> 1) < (lq0 == 0 ? 8 : NWL)) issue_one(ls, lq0 + (q >> 1));
+                    const int nl = lq0 == 0 ? NAL : NWL;
+                    if ((q >> 1) < nl) issue_one(ls, lq0 + (q >> 1));
+                    if (SLOTS / 2 < nl && q >= SLOTS - 3) issue_one(ls, lq0 + nl - (q == SLOTS - 3 ? 2 : 1));
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -553,9 +572,9 @@ __global__ __launch_bounds__(256) void prefill_w4_kernel(PrefillParams p) {
     auto quad_pack = [&](int i, int j, int g) -> uint2 {
         // the four sums, read out of their AGPRs here (an asm the compiler
         // cannot move, so the reads of one MFMA tile happen where it is used);
-        // the fifth column's sums are VGPRs already
+        // the fifth column's (or row's) sums are VGPRs already
         float f0, f1, f2, f3;
-        if (j < 4) {
+        if (i < 4 && j < 4) {
             asm volatile("v_accvgpr_read_b32 %0, %4\n\tv_accvgpr_read_b32 %1, %5\n\t"
                          "v_accvgpr_read_b32 %2, %6\n\tv_accvgpr_read_b32 %3, %7"
                          : "=v"(f0), "=v"(f1), "=v"(f2), "=v"(f3)
@@ -590,7 +609,7 @@ __global__ __launch_bounds__(256) void prefill_w4_kernel(PrefillParams p) {
     for (int q = 0; q < NLOAD; ++q) issue_one(0, q);
     if (WST == 3 && KT > 1)
 #pragma unroll
-        for (int q = 8; q < NLOAD; ++q) issue_one(1, q);
+        for (int q = NAL; q < NLOAD; ++q) issue_one(1, q);
     for (;;) {
         // step 0 loaded and visible (three weight stages: step 1's weight
         // tile, issued after it, may stay in flight), its first fragments
@@ -602,12 +621,12 @@ __global__ __launch_bounds__(256) void prefill_w4_kernel(PrefillParams p) {
         for (int q = 0; q < NREAD; ++q) fread_one(0, 0, q, fa0, fb0);
         if (KT > 1)
 #pragma unroll
-            for (int q = 0; q < 8; ++q) issue_one(1, q);
+            for (int q = 0; q < NAL; ++q) issue_one(1, q);
         int s = 0;
         for (; s + 2 < KT; ++s) {            // steady state: every load present
             // the weight tile of step s + WST - 1 (two stages: the rest of
             // step s + 1; three: step s + 2, into the stage step s - 1 read)
-            substep(Y, Y, fa0, fb0, s, 1, fa1, fb1, s + WST - 1, 8);
+            substep(Y, Y, fa0, fb0, s, 1, fa1, fb1, s + WST - 1, NAL);
             substep(Y, N, fa1, fb1, s, 2, fa0, fb0, 0, 0);
             substep(Y, N, fa0, fb0, s, 3, fa1, fb1, 0, 0);
             // step s + 1 landed (three stages: step s + 2's weight tile,
@@ -633,11 +652,11 @@ __global__ __launch_bounds__(256) void prefill_w4_kernel(PrefillParams p) {
                 // KT - 3 read (g_ld: the next unit's g)
                 set_w_rows(nn0);
                 g_ld = g_rd + KT;
-                substep(Y, Y, fa0, fb0, s, 1, fa1, fb1, 0, 8);
+                substep(Y, Y, fa0, fb0, s, 1, fa1, fb1, 0, NAL);
             } else if constexpr (WST == 3) {
                 substep(Y, N, fa0, fb0, s, 1, fa1, fb1, 0, 0);   // step KT - 1's weight is in flight already
             } else {
-                substep(Y, Y, fa0, fb0, s, 1, fa1, fb1, s + 1, 8);
+                substep(Y, Y, fa0, fb0, s, 1, fa1, fb1, s + 1, NAL);
             }
             substep(Y, N, fa1, fb1, s, 2, fa0, fb0, 0, 0);
             substep(Y, N, fa0, fb0, s, 3, fa1, fb1, 0, 0);
@@ -660,7 +679,7 @@ __global__ __launch_bounds__(256) void prefill_w4_kernel(PrefillParams p) {
         // the last step (PERSIST: the next unit's weight tile of step 1 with
         // three stages, of step 0 with two; a persistent unit has at least
         // two K steps, so step KT - 2 above ran)
-        if constexpr (PERSIST) substep(Y, Y, fa0, fb0, s, 1, fa1, fb1, WST == 3 ? 1 : 0, 8);
+        if constexpr (PERSIST) substep(Y, Y, fa0, fb0, s, 1, fa1, fb1, WST == 3 ? 1 : 0, NAL);
         else substep(Y, N, fa0, fb0, s, 1, fa1, fb1, 0, 0);
         substep(Y, N, fa1, fb1, s, 2, fa0, fb0, 0, 0);
         substep(Y, N, fa0, fb0, s, 3, fa1, fb1, 0, 0);
@@ -703,9 +722,27 @@ __global__ __launch_bounds__(256) void prefill_w4_kernel(PrefillParams p) {
         } else {
             // D layout of a 32x32 MFMA tile: lane l, register v holds
             // row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32
-            if constexpr (OUT_BF16) {
+            if constexpr (OUT_BF16 && DIRECT) {
+                // 320 rows: straight from registers, 8 bytes of one row per
+                // lane (N is a whole number of tiles: the planner's condition)
+                mfma_settle();
+                uint16_t* C = static_cast<uint16_t*>(p.C);
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) {
+#pragma unroll
+                        for (int g = 0; g < 4; ++g) {
+                            const uint2 v = quad_pack(i, j, g);
+                            const int row = m0 + wm * (32 * MI) + i * 32 + 8 * g + 4 * (lane >> 5) + qrow;
+                            if (row < p.M)
+                                *reinterpret_cast<uint2*>(C + int64_t(row) * p.ldc + n0 + wn * (32 * NJ) + j * 32 + cquad) = v;
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+            } else if constexpr (OUT_BF16) {
                 // through LDS (the operand stages are free once every wave is
-                // past its last MFMA): the 256 x 256 bf16 tile with 576-byte
+                // past its last MFMA): the bf16 tile with 576-byte
                 // rows, each lane writing its quad-transposed 8 bytes (the
                 // stride puts a quad's four rows in four distinct 64-byte bank
                 // ranges), then 16-byte stores of eight consecutive columns
@@ -715,19 +752,19 @@ __global__ __launch_bounds__(256) void prefill_w4_kernel(PrefillParams p) {
                 mfma_settle();
                 uint8_t* Cs = smem;
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < MI; ++i)
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
 #pragma unroll
                         for (int g = 0; g < 4; ++g) {
-                            const int r = wm * 128 + i * 32 + 8 * g + 4 * (lane >> 5) + qrow;
+                            const int r = wm * (32 * MI) + i * 32 + 8 * g + 4 * (lane >> 5) + qrow;
                             const int c = wn * 128 + j * 32 + cquad;
                             *reinterpret_cast<uint2*>(Cs + r * CS + c * 2) = quad_pack(i, j, g);
                             __builtin_amdgcn_sched_barrier(0);
                         }
                 __syncthreads();
                 uint16_t* C = static_cast<uint16_t*>(p.C);
-                for (int e = t; e < 256 * 32; e += 256) {
+                for (int e = t; e < BM * 32; e += 256) {
                     const int r = e >> 5, c = (e & 31) * 8;
                     const int row = m0 + r, col = n0 + c;
                     if (row >= p.M) continue;
@@ -742,15 +779,22 @@ __global__ __launch_bounds__(256) void prefill_w4_kernel(PrefillParams p) {
                     }
                 }
             } else {
-                // fp32 output, or this split's fp32 partial (row stride N)
+                // fp32 output, or this split's fp32 partial (row stride N);
+                // 320 rows: the fifth row's last MFMAs are inline assembly,
+                // so their results are waited for here
+                if constexpr (MI == 5) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    mfma_settle();
+                    __builtin_amdgcn_sched_barrier(0);
+                }
                 const bool full = m0 + BM <= p.M && n0 + BN <= p.N;
-                const int row_base = m0 + wm * 128 + 4 * (lane >> 5);
+                const int row_base = m0 + wm * (32 * MI) + 4 * (lane >> 5);
                 const int col_base = n0 + wn * 128 + (lane & 31);
                 const bool part = p.split_k > 1;
                 float* C = part ? p.ws + int64_t(split) * p.ws_stride : static_cast<float*>(p.C);
                 const int64_t ldc = part ? int64_t(p.N) : p.ldc;
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < MI; ++i)
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         float* Cij = C + int64_t(row_base + i * 32) * ldc + col_base + j * 32;
@@ -800,6 +844,23 @@ hipError_t launch_t(const PrefillParams& p, int grid, bool tile, hipStream_t s) 
     else if (p.log2_fetch > 0)
         hipLaunchKernelGGL((prefill_kernel<BM, BN, WGM, WGN, false, true>), dim3(grid), dim3(64 * WGM * WGN), 0, s, p);
     else hipLaunchKernelGGL((prefill_kernel<BM, BN, WGM, WGN, false>), dim3(grid), dim3(64 * WGM * WGN), 0, s, p);
+    return hipGetLastError();
+}
+
+// prefill_w4_kernel outside the persistent grid: 192, 256 or 320 x 256 tiles
+template <bool OUT_BF16>
+hipError_t launch_w4(const PrefillParams& p, int grid, int tile_m, bool tile, hipStream_t s) {
+    const dim3 g(grid), b(256);
+    if (tile_m == 192) {
+        if (tile) hipLaunchKernelGGL((prefill_w4_kernel<true, OUT_BF16, false, 4, 3>), g, b, 0, s, p);
+        else hipLaunchKernelGGL((prefill_w4_kernel<false, OUT_BF16, false, 4, 3>), g, b, 0, s, p);
+    } else if (tile_m == 320) {
+        if (tile) hipLaunchKernelGGL((prefill_w4_kernel<true, OUT_BF16, false, 4, 5>), g, b, 0, s, p);
+        else hipLaunchKernelGGL((prefill_w4_kernel<false, OUT_BF16, false, 4, 5>), g, b, 0, s, p);
+    } else {
+        if (tile) hipLaunchKernelGGL((prefill_w4_kernel<true, OUT_BF16>), g, b, 0, s, p);
+        else hipLaunchKernelGGL((prefill_w4_kernel<false, OUT_BF16>), g, b, 0, s, p);
+    }
     return hipGetLastError();
 }
 
@@ -860,16 +921,15 @@ hipError_t launch_range(const PrefillLaunch& q, int64_t n_begin, int64_t n_cols,
                     hipLaunchKernelGGL((prefill_w4_kernel<false, true, true>), dim3(pgrid), dim3(256), 0, stream, p);
                 return hipGetLastError();
             }
-            if (tile) {
-                if (p.out_bf16) hipLaunchKernelGGL((prefill_w4_kernel<true, true>), dim3(grid), dim3(256), 0, stream, p);
-                else hipLaunchKernelGGL((prefill_w4_kernel<true, false>), dim3(grid), dim3(256), 0, stream, p);
-            } else {
-                if (p.out_bf16) hipLaunchKernelGGL((prefill_w4_kernel<false, true>), dim3(grid), dim3(256), 0, stream, p);
-                else hipLaunchKernelGGL((prefill_w4_kernel<false, false>), dim3(grid), dim3(256), 0, stream, p);
-            }
-            return hipGetLastError();
+            return p.out_bf16 ? launch_w4<true>(p, grid, 256, tile, stream) : launch_w4<false>(p, grid, 256, tile, stream);
         }
         return launch_t<256, 256, 2, 4>(p, grid, tile, stream);
+    }
+    // 192 or 320 rows x 256 columns (K % 64 == 0, N % 256 == 0, no block
+    // emulation: the planner's conditions)
+    if (tile_n == 256 && (tile_m == 192 || tile_m == 320)) {
+        if (q.K % 64 || n_cols % 256 || p.log2_fetch) return hipErrorInvalidValue;
+        return p.out_bf16 ? launch_w4<true>(p, grid, tile_m, tile, stream) : launch_w4<false>(p, grid, tile_m, tile, stream);
     }
     if (tile_m == 256) return launch_t<256, 128, 2, 2>(p, grid, tile, stream);
     return launch_t<128, 128, 2, 2>(p, grid, tile, stream);
@@ -882,7 +942,7 @@ hipError_t launch_prefill(const PrefillLaunch& q, hipStream_t stream) {
     hipError_t e = q.n_main > 0 ? launch_range(q, 0, q.n_main, q.tile_m, q.tile_n, stream) : hipSuccess;
     if (e != hipSuccess || q.n_main == q.N) return e;
     if (q.split_rest <= 1) return launch_range(q, q.n_main, q.N - q.n_main, 128, 128, stream);
-    // the remaining columns: 256 x 256 tiles of prefill_w4_kernel, K split
+    // the remaining columns: tile_m x 256 tiles of prefill_w4_kernel, K split
     // split_rest ways (fp32 partials in ws), then the fixed-order reduce
     const bool tile = q.L.kind == TL_LAYOUT_TILE;
     const int64_t kp = tile ? padded_cols(q.L, q.K) : q.K;
@@ -896,7 +956,7 @@ hipError_t launch_prefill(const PrefillLaunch& q, hipStream_t stream) {
     p.N = int(n_cols);
     p.K = int(q.K);
     p.ldc = q.N;
-    p.m_tiles = int((q.M + 255) / 256);
+    p.m_tiles = int((q.M + q.tile_m - 1) / q.tile_m);
     p.strip_bytes = tile ? q.L.br * kp * 2 : 0;
     p.log2_br = tile ? q.L.log2_br : 0;
     p.log2_bc = tile ? q.L.log2_bc : 0;
@@ -910,9 +970,7 @@ hipError_t launch_prefill(const PrefillLaunch& q, hipStream_t stream) {
     p.ws = q.ws;
     p.ws_stride = q.M * n_cols;
     const int grid = int(p.m_tiles * ((n_cols + 255) / 256) * q.split_rest);
-    if (tile) hipLaunchKernelGGL((prefill_w4_kernel<true, false>), dim3(grid), dim3(256), 0, stream, p);
-    else hipLaunchKernelGGL((prefill_w4_kernel<false, false>), dim3(grid), dim3(256), 0, stream, p);
-    e = hipGetLastError();
+    e = launch_w4<false>(p, grid, q.tile_m, tile, stream);
     if (e != hipSuccess) return e;
     uint8_t* c0 = static_cast<uint8_t*>(q.C) + q.n_main * (q.out_bf16 ? 2 : 4);
     const int rgrid = int((q.M * n_cols / 4 + 255) / 256);

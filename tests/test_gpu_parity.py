@@ -934,3 +934,30 @@ def test_row_adaptive_edges(M, N, K, row_major):
     parity(host_f32(tl.gemm(dev_bf16(A), Wd, N, d, fetch)), y_ref, "f32")
     db = tl.layout(kind=kind, G=1024, block_rows=16, out_dtype=tl.TL_OUT_BF16)
     parity_bf16_out(host_bits(tl.gemm(dev_bf16(A), Wd, N, db, fetch)), y_ref, "bf16")
+
+
+# 192- and 320-row tiles of the four-wave prefill kernel, where the plan takes
+# them: one and several row tiles, the last of them ragged, with K split and
+# without, one K step per split more or less, a row-major weight.
+@pytest.mark.parametrize("M,N,K,row_major,tm,S", [
+    (300, 57344, 128, False, 320, 1), (257, 57344, 192, True, 320, 1), (577, 24576, 192, False, 320, 1),
+    (384, 57344, 64, True, 192, 1), (576, 57344, 64, False, 192, 1),
+    (300, 8192, 4096, False, 192, 3), (321, 8192, 4160, True, 192, 3), (300, 2560, 16384, False, 192, 8),
+    (300, 8192, 16384, False, 320, 6),
+])
+def test_prefill_192_and_320_row_tiles(M, N, K, row_major, tm, S):
+    kind = tl.TL_LAYOUT_NK_ROW if row_major else tl.TL_LAYOUT_TILE
+    fetch = tl.TL_FETCH_NATIVE if row_major else tl.TL_FETCH_BLOCK
+    d, db = tl.layout(kind=kind), tl.layout(kind=kind, out_dtype=tl.TL_OUT_BF16)
+    plan = tl.tl_gemm_plan(M, N, K, d, fetch)
+    banner(f"prefill {tm}-row tiles M={M} N={N} K={K} row_major={row_major} plan={plan}")
+    assert (plan["tile_m"], plan["tile_n"], plan["split_k"]) == (tm, 256, S)
+    assert plan["workgroups"] == -(-M // tm) * (N // 256) * S
+    A = synth.normal_bf16((M, K), seed=190 + M)
+    W = synth.normal_bf16((N, K), seed=191, sigma=synth.W_SIGMA)
+    y_ref = oracle.gemm_f64(A, W)
+    C1 = host_f32(run_gemm(A, W, d, fetch=fetch, tile_major=not row_major))
+    parity(C1, y_ref, "f32")
+    got = host_bits(run_gemm(A, W, db, fetch=fetch, tile_major=not row_major))
+    parity_bf16_out(got, y_ref, "bf16")
+    assert np.array_equal(got, oracle.round_bf16(C1.astype(np.float64)))   # the same sums, rounded
