@@ -37,7 +37,8 @@ int make_tile_layout(int64_t s, int64_t G, int64_t br, Layout* out) {
 namespace {
 
 // ---------------------------------------------------------------------------
-// Library state: split-K workspace and the fetch tally, one set per
+// Library state: split-K workspace, the fetch tally and the arrival counters
+// of K splits summed inside a launch (zero between calls), one set per
 // (device, stream).  A workspace that has to grow is retired, not freed: a
 // HIP graph captured earlier on the stream, or a call of another thread that
 // took the old pointer, may still use it.  Retired workspaces are freed by
@@ -48,7 +49,7 @@ struct StreamState {
     int dev = 0;
     float* ws = nullptr;
     size_t ws_bytes = 0;
-    unsigned long long* fetch = nullptr;
+    unsigned long long* fetch = nullptr;   // kStateWords: the tally, then the counters
     std::vector<float*> retired;
     ~StreamState() {
         int cur = 0;
@@ -66,7 +67,14 @@ struct StateRef {
     std::shared_ptr<StreamState> keep;
     float* ws = nullptr;
     unsigned long long* fetch = nullptr;
+    unsigned* arrive = nullptr;
 };
+
+// tiles with a counter (64 bytes apart: 16 words); launches with more K-split
+// tiles, and tl_gemm_noalloc, sum their partials in a second launch
+constexpr int kArriveTiles = 2048;
+constexpr int kArriveAt = 8;              // in 8-byte words from the tally
+constexpr int kStateWords = kArriveAt + kArriveTiles * 8;
 
 std::mutex g_mu;
 std::map<std::pair<int, void*>, std::shared_ptr<StreamState>> g_state;
@@ -75,8 +83,8 @@ int current_device(int* dev) {
     return hipGetDevice(dev) == hipSuccess ? TL_OK : TL_EHIP;
 }
 
-// Looks up (current device, stream), creating its tally (cleared on 'stream',
-// so the clear is ordered before any kernel that uses it) and growing its
+// Looks up (current device, stream), creating its tally and counters (cleared
+// on 'stream', so the clear is ordered before any kernel that uses it) and growing its
 // workspace to at least ws_bytes.  The lock covers the map and the
 // allocations only; nothing here waits for the GPU.
 int get_state(hipStream_t stream, size_t ws_bytes, StateRef* out) {
@@ -90,8 +98,8 @@ int get_state(hipStream_t stream, size_t ws_bytes, StateRef* out) {
     }
     StreamState& st = *sp;
     if (!st.fetch) {
-        if (hipMalloc(&st.fetch, sizeof(unsigned long long)) != hipSuccess) { st.fetch = nullptr; return TL_ENOMEM; }
-        if (launch_zero_u64(st.fetch, stream) != hipSuccess) {   // the next call allocates and clears again
+        if (hipMalloc(&st.fetch, kStateWords * sizeof(unsigned long long)) != hipSuccess) { st.fetch = nullptr; return TL_ENOMEM; }
+        if (launch_zero_u64(st.fetch, kStateWords, stream) != hipSuccess) {   // the next call allocates and clears again
             (void)hipFree(st.fetch);
             st.fetch = nullptr;
             return TL_EHIP;
@@ -110,6 +118,7 @@ int get_state(hipStream_t stream, size_t ws_bytes, StateRef* out) {
     out->keep = sp;
     out->ws = st.ws;
     out->fetch = st.fetch;
+    out->arrive = reinterpret_cast<unsigned*>(st.fetch + kArriveAt);
     return TL_OK;
 }
 
@@ -847,6 +856,18 @@ static int gemm_impl(const void* A, const void* W, const float* scales, void* C,
         d.C = C;
         d.ws = st.ws;
         d.fetch = p.count ? st.fetch : nullptr;
+        // A small weight's call is a few microseconds, of which a second
+        // launch takes 2.5 on the host and 1 - 2 on the GPU: its K splits are
+        // summed inside the launch, as long as one workgroup reads a tile's
+        // partials quickly (4096 floats; one MI355X, eager / in a graph, us:
+        // 1 x 1024 x 1024 10.9 -> 7.8 / 5.7 -> 5.4, 16 x 1024 x 4096, S = 8:
+        // 10.1 -> 7.5 / 7.7 -> 7.1; past the line 64 x 512 x 7168, S = 14:
+        // 10.3 against 12.5 / 10.0 against 12.5).  On large weights every
+        // workgroup would hold its CU while its partials are written out
+        // (Llama-70B layer at M = 8: 260 against 267 us).
+        if (p.pub.split_k > 1 && !p.lds_tiles && N * K * layout->elem_bytes < (int64_t(32) << 20) &&
+            M * p.pub.tile_n * p.pub.split_k <= 4096 && p.pub.workgroups / p.pub.split_k <= kArriveTiles)
+            d.arrive = st.arrive;
         d.M = M;
         d.N = N;
         d.K = K;
@@ -1120,7 +1141,7 @@ int tl_fetch_counter_read(void* stream, int64_t* bytes) {
     unsigned long long v = 0;
     if (hipStreamSynchronize(s) != hipSuccess) return TL_EHIP;
     if (hipMemcpy(&v, st.fetch, sizeof v, hipMemcpyDeviceToHost) != hipSuccess) return TL_EHIP;
-    if (launch_zero_u64(st.fetch, s) != hipSuccess) return TL_EHIP;
+    if (launch_zero_u64(st.fetch, 1, s) != hipSuccess) return TL_EHIP;
     if (hipStreamSynchronize(s) != hipSuccess) return TL_EHIP;
     *bytes = int64_t(v);
     return TL_OK;

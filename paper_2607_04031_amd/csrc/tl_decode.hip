@@ -334,9 +334,13 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kernel(DecodeParams p) {
             if (m < crows && n < p.N) {
                 const int64_t row = GROUPED ? int64_t(row0 + mc + m) : int64_t(m);
                 if (final_out) store_out(p.C, row * p.N + n, v[r], p.out_bf16);
+                else if (!GROUPED && p.arrive) store_partial(part + row * p.N + n, v[r]);
                 else part[row * p.N + n] = v[r];
             }
         }
+    }
+    if constexpr (!GROUPED) {
+        if (!final_out && p.arrive) splitk_finish<TN, kThreads>(p, tile, n_base);
     }
     if constexpr (!GROUPED) break;
     mc += 16 * MT;
@@ -378,7 +382,9 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* ws, voi
     }
 }
 
-__global__ void zero_u64_kernel(unsigned long long* p) { *p = 0ull; }
+__global__ void zero_u64_kernel(unsigned long long* p, int n) {
+    for (int i = threadIdx.x; i < n; i += 256) p[i] = 0ull;
+}
 
 template <int MT, int NS, int WAVES, bool TILE, bool GROUPED, bool SWIGLU = false>
 hipError_t launch_t(const DecodeParams& p, int grid, hipStream_t stream) {
@@ -432,8 +438,8 @@ hipError_t launch_m(const DecodeParams& p, int grid, int ns, int waves, bool til
 
 }  // namespace
 
-hipError_t launch_zero_u64(unsigned long long* p, hipStream_t stream) {
-    hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(1), 0, stream, p);
+hipError_t launch_zero_u64(unsigned long long* p, int n, hipStream_t stream) {
+    hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(256), 0, stream, p, n);
     return hipGetLastError();
 }
 
@@ -471,6 +477,7 @@ hipError_t launch_decode(const DecodeLaunch& d, hipStream_t stream) {
     p.a_rows = int(d.a_rows);
     p.total_rows = int(d.total_rows);
     p.scales = d.scales;
+    p.arrive = d.split_k > 1 ? d.arrive : nullptr;
     if (d.lds_tiles > 0) {   // workgroup = lds_tiles tiles x one K range
         const int grid = int(d.N / 32 / d.lds_tiles) * d.split_k;
         return launch_splitk_reduce(d, launch_lds_decode(p, d.lds_tiles, grid, stream), stream);
@@ -491,7 +498,7 @@ hipError_t launch_decode(const DecodeLaunch& d, hipStream_t stream) {
 }
 
 hipError_t launch_splitk_reduce(const DecodeLaunch& d, hipError_t e, hipStream_t stream) {
-    if (e != hipSuccess || d.split_k == 1) return e;
+    if (e != hipSuccess || d.split_k == 1 || d.arrive) return e;
     const int64_t mn = d.M * d.N, stride = (mn + 3) / 4 * 4;
     const int rgrid = int((stride / 4 + 255) / 256);
     if (d.out_bf16)

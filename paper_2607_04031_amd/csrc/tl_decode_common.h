@@ -41,6 +41,7 @@ struct DecodeParams {
     int a_rows;              // rows of A; token ids outside [0, a_rows) read zeros
     int total_rows;          // rows of C; group offsets are clamped to [0, total_rows]
     const float* scales;     // FP8 weights: per-output-channel scale [N], or nullptr (1)
+    unsigned* arrive;        // K splits summed inside the launch: one arrival counter per tile, else nullptr
     int swiglu_up;           // gated grouped launch: row of the first up row (I); C has N = I columns
 };
 
@@ -76,6 +77,89 @@ __device__ inline bf16x8 swap8(bf16x8 v) {
 
 __device__ inline bf16x8 load_stream(const uint8_t* p) {
     return __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(p));
+}
+
+// K splits summed inside the launch (p.arrive): every workgroup stores its
+// fp32 partial, waits until it is out and counts itself at its tile's counter;
+// the workgroup that finds all the others' there sums the tile's partials in
+// split order -- the same sums, bit for bit, as splitk_reduce_kernel -- and
+// leaves the counter at zero for the next call.  Nobody waits for another
+// workgroup.  The splits of a tile run on different XCDs, whose L2s are not
+// coherent with each other, so partials are written through and read past
+// them (agent scope) instead of writing back a whole L2 at a fence.
+constexpr int kArriveStride = 16;        // counters are 64 bytes apart
+
+__device__ inline void store_partial(float* p, float v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Columns [n0, n0 + COLS) of C (n0 a multiple of 4), after this workgroup's
+// partials of them were stored.  Every thread of the workgroup calls it.
+template <int COLS, int THREADS>
+__device__ inline void splitk_finish(const DecodeParams& p, int tile, int n0) {
+    __shared__ unsigned arrived;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // this wave's partials are out
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned* cnt = p.arrive + tile * kArriveStride;
+        const unsigned before = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (before == unsigned(p.split_k) - 1) __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        arrived = before;
+    }
+    __syncthreads();
+    if (arrived != unsigned(p.split_k) - 1) return;     // uniform over the workgroup
+    constexpr int kAhead = 8;                           // partials in flight per thread
+    if (p.N % 4 == 0) {
+        typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
+        for (int e = threadIdx.x; e < p.M * (COLS / 4); e += THREADS) {
+            const int m = e / (COLS / 4), n = n0 + e % (COLS / 4) * 4;
+            if (n >= p.N) continue;
+            const int64_t at = int64_t(m) * p.N + n;
+            f32x4 v = {0.f, 0.f, 0.f, 0.f};
+            for (int s0 = 0; s0 < p.split_k; s0 += kAhead) {
+                u64x2 x[kAhead];
+#pragma unroll
+                for (int s = 0; s < kAhead; ++s)
+                    if (s0 + s < p.split_k) {
+                        unsigned long long* src = reinterpret_cast<unsigned long long*>(p.ws + (s0 + s) * p.ws_stride + at);
+                        x[s][0] = __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        x[s][1] = __hip_atomic_load(src + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+#pragma unroll
+                for (int s = 0; s < kAhead; ++s)
+                    if (s0 + s < p.split_k) {
+                        const f32x4 part = __builtin_bit_cast(f32x4, x[s]);
+                        v = s0 + s == 0 ? part : v + part;
+                    }
+            }
+            if (p.out_bf16) {
+                uint2 o;
+                o.x = uint32_t(f32_to_bf16_rne(v[0])) | (uint32_t(f32_to_bf16_rne(v[1])) << 16);
+                o.y = uint32_t(f32_to_bf16_rne(v[2])) | (uint32_t(f32_to_bf16_rne(v[3])) << 16);
+                *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.C) + at) = o;
+            } else {
+                *reinterpret_cast<f32x4*>(static_cast<float*>(p.C) + at) = v;
+            }
+        }
+    } else {
+        for (int e = threadIdx.x; e < p.M * COLS; e += THREADS) {
+            const int m = e / COLS, n = n0 + e % COLS;
+            if (n >= p.N) continue;
+            const int64_t at = int64_t(m) * p.N + n;
+            float v = 0.f;
+            for (int s0 = 0; s0 < p.split_k; s0 += kAhead) {
+                float x[kAhead];
+#pragma unroll
+                for (int s = 0; s < kAhead; ++s)
+                    if (s0 + s < p.split_k)
+                        x[s] = __hip_atomic_load(p.ws + (s0 + s) * p.ws_stride + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                for (int s = 0; s < kAhead; ++s)
+                    if (s0 + s < p.split_k) v = s0 + s == 0 ? x[s] : v + x[s];
+            }
+            store_out(p.C, at, v, p.out_bf16);
+        }
+    }
 }
 
 // FP8-weight decode (tl_decode_fp8.hip): launches decode_fp8_kernel for the

@@ -169,10 +169,12 @@ __global__ __launch_bounds__(64 * WAVES) void decode_fp8_kernel(DecodeParams p) 
             const int m = mt * 16 + (l >> 4) * 4 + r;
             if (m < p.M && n < p.N) {
                 if (final_out) store_out(p.C, int64_t(m) * p.N + n, v[r] * sc, p.out_bf16);
+                else if (p.arrive) store_partial(part + int64_t(m) * p.N + n, v[r] * sc);
                 else part[int64_t(m) * p.N + n] = v[r] * sc;
             }
         }
     }
+    if (!final_out && p.arrive) splitk_finish<TN, kThreads>(p, tile, n_base);
 }
 
 template <int MT, int NS, int WAVES, bool TILE>

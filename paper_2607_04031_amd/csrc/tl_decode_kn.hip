@@ -193,10 +193,12 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kn_kernel(DecodeParams p) {
             const int m = mt * 16 + (l >> 4) * 4 + r;
             if (m < p.M && n < p.N) {
                 if (final_out) store_out(p.C, int64_t(m) * p.N + n, v[r], p.out_bf16);
+                else if (p.arrive) store_partial(part + int64_t(m) * p.N + n, v[r]);
                 else part[int64_t(m) * p.N + n] = v[r];
             }
         }
     }
+    if (!final_out && p.arrive) splitk_finish<64, kThreads>(p, tile, n0);
 }
 
 template <int MT, int WAVES>

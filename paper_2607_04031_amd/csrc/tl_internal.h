@@ -55,6 +55,7 @@ struct DecodeLaunch {
     void* C;
     float* ws;                  // [split_k][M * N rounded up to 4] partials (split_k > 1)
     unsigned long long* fetch;  // fetch tally (TL_FETCH_COUNT) or nullptr
+    unsigned* arrive = nullptr; // zeroed arrival counters, one per tile: K splits summed inside the launch
     int64_t M, N, K;
     Layout L;
     int tile_n;                 // 32 or 64
@@ -86,7 +87,7 @@ struct DecodeLaunch {
 hipError_t launch_decode(const DecodeLaunch& d, hipStream_t stream);
 // *p = 0, enqueued on 'stream' as a one-thread kernel (not a memset node, so
 // the clear behaves like any kernel inside a captured graph)
-hipError_t launch_zero_u64(unsigned long long* p, hipStream_t stream);
+hipError_t launch_zero_u64(unsigned long long* p, int n, hipStream_t stream);
 // the fixed-order split-K reduce that follows a decode launch with split_k > 1
 // (passes 'e' through when it is an error or split_k is 1)
 hipError_t launch_splitk_reduce(const DecodeLaunch& d, hipError_t e, hipStream_t stream);
