@@ -136,7 +136,9 @@ typedef struct tl_plan {
     int32_t waves;       /* wavefronts per workgroup (decode: 4, 8 or 16; the
                             waves of a workgroup also split K, reduced in LDS) */
     int64_t workgroups;  /* grid size, summed over the call's launches (a
-                            persistent prefill grid: at most 256) */
+                            persistent prefill grid: at most 256; over a
+                            [K][N] weight: column tiles times splits, four
+                            neighbouring tiles may share a workgroup) */
     int64_t workspace_bytes;  /* split-K partials the call needs from the library */
 } tl_plan;
 

@@ -171,6 +171,7 @@ struct Plan {
     int64_t n_main = 0;          // prefill: columns covered by the main tiles (rest: 128 x 128)
     bool fp8 = false;            // 1-byte (OCP E4M3) weight, decode kernel
     int lds_tiles = 0;           // > 0: decode with activations staged in LDS, tiles per workgroup
+    bool kn_wide = false;        // that kernel with 256 columns per workgroup
     bool kn_row = false;         // weight stored [K][N] (N contiguous): the transposing decode kernel
     int split_rest = 0;          // prefill: K splits of the 256 x 256 tiles past n_main (0: 128 x 128 tiles)
     bool persist = false;        // prefill: one workgroup per CU walks the main launch's tiles
@@ -298,12 +299,34 @@ int plan_gemm(int64_t M, int64_t N, int64_t K, const tl_layout_desc* d, int32_t 
         if (S < 1 || S > units || S > kMaxSplitK) return TL_EUNSUPPORTED;
         const int64_t wgs = n_tiles * S;
         p.waves = (wgs <= 2 * kCUs && p.m_tiles16 <= 2) ? 8 : 4;
-        p.pub.tile_m = 16 * p.m_tiles16;
         p.pub.tile_n = 64;
+        // M <= 32, nothing requested: 256-column tiles with the K split that
+        // gives one round of the CUs, where that fills two thirds of it with
+        // >= 1024 K per split (45056 x 4096, 176 workgroups: 72 -> 65 us;
+        // 24576 x 4096, 192: 40 -> 37; 2048 x 8192, whose 64 workgroups do
+        // not: 12 against 29).  Past one round two workgroups share a CU, and
+        // tiles that fill 7/10 of those rounds take it (98304 x 2048, 384
+        // tiles: 77 -> 73; 81920 x 4096, 320: 122 against 130); so do 129 -
+        // 170 tiles of rows that are not whole lines, in three splits (35000 x
+        // 8192: 181 -> 146; 40000 x 4096, whole lines: 54 against 56).  At four
+        // M tiles the sums do not leave registers for it (8192 x 28672, M =
+        // 48: 119 against 220).  tile_n and workgroups report 64-column tiles
+        if (p.m_tiles16 <= 2 && !d->split_k && !d->tile_n && !p.block_row) {
+            const int64_t wide = (N + 255) / 256, max_s = std::max<int64_t>(1, std::min<int64_t>(units / 16, kMaxSplitK));
+            int64_t s1 = std::max<int64_t>(1, std::min(kCUs / wide, max_s));
+            if (N % 64 && wide > kCUs / 2 && 3 * wide <= 2 * kCUs && max_s >= 3) s1 = 3;
+            const int64_t pairs = (wide + 2 * kCUs - 1) / (2 * kCUs);   // rounds of two workgroups per CU
+            if (wide <= kCUs ? 3 * wide * s1 >= 2 * kCUs : 10 * wide >= 14 * kCUs * pairs) {
+                S = s1;
+                p.waves = 8;
+                p.kn_wide = true;
+            }
+        }
+        p.pub.tile_m = 16 * p.m_tiles16;
         p.pub.tile_k = 64;
         p.pub.split_k = int(S);
         p.pub.waves = p.waves;
-        p.pub.workgroups = wgs;
+        p.pub.workgroups = n_tiles * S;
         p.pub.workspace_bytes = S > 1 ? S * ((M * N + 3) / 4 * 4) * 4 : 0;
     } else if (M <= kDecodeMaxM && d->tile_m <= 64 && !wide_mid_m) {
         p.pub.kernel = 1;
@@ -864,9 +887,11 @@ static int gemm_impl(const void* A, const void* W, const float* scales, void* C,
         // 10.1 -> 7.5 / 7.7 -> 7.1; past the line 64 x 512 x 7168, S = 14:
         // 10.3 against 12.5 / 10.0 against 12.5).  On large weights every
         // workgroup would hold its CU while its partials are written out
-        // (Llama-70B layer at M = 8: 260 against 267 us).
-        if (p.pub.split_k > 1 && !p.lds_tiles && N * K * layout->elem_bytes < (int64_t(32) << 20) &&
-            M * p.pub.tile_n * p.pub.split_k <= 4096 && p.pub.workgroups / p.pub.split_k <= kArriveTiles)
+        // (Llama-70B layer at M = 8: 260 against 267 us).  More than 512
+        // workgroups (4 waves) and the block emulation keep the second launch.
+        if (p.pub.split_k > 1 && p.waves >= 8 && !p.block_row && !p.lds_tiles && !p.kn_wide &&
+            N * K * layout->elem_bytes < (int64_t(32) << 20) && M * p.pub.tile_n * p.pub.split_k <= 4096 &&
+            p.pub.workgroups / p.pub.split_k <= kArriveTiles)
             d.arrive = st.arrive;
         d.M = M;
         d.N = N;
@@ -883,6 +908,7 @@ static int gemm_impl(const void* A, const void* W, const float* scales, void* C,
         d.fp8 = p.fp8;
         d.scales = scales;
         d.lds_tiles = p.lds_tiles;
+        d.kn_wide = p.kn_wide;
         e = launch_decode(d, s);
     } else {
         PrefillLaunch q;

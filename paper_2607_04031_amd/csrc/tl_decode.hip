@@ -62,7 +62,7 @@ namespace {
 // as subtiles 0-1 and the up rows I + [32 t, 32 t + 32) as subtiles 2-3 --
 // two whole 32-row strips -- and writes C[r][32 t + c] = silu(g) * u for its
 // 32 columns (C has I columns).
-template <int MT, int NS, int U, int WAVES, bool TILE, bool BLOCKROW, bool GROUPED, bool SWIGLU = false>
+template <int MT, int NS, int U, int WAVES, bool TILE, bool BLOCKROW, bool GROUPED, bool SWIGLU = false, bool FUSE = false>
 __global__ __launch_bounds__(64 * WAVES) void decode_kernel(DecodeParams p) {
     static_assert(!SWIGLU || (GROUPED && NS == 4), "gated launches are grouped, 32 gate + 32 up rows");
     constexpr int kWaves = WAVES;
@@ -334,14 +334,12 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kernel(DecodeParams p) {
             if (m < crows && n < p.N) {
                 const int64_t row = GROUPED ? int64_t(row0 + mc + m) : int64_t(m);
                 if (final_out) store_out(p.C, row * p.N + n, v[r], p.out_bf16);
-                else if (!GROUPED && p.arrive) store_partial(part + row * p.N + n, v[r]);
+                else if (FUSE) store_partial(part + row * p.N + n, v[r]);
                 else part[row * p.N + n] = v[r];
             }
         }
     }
-    if constexpr (!GROUPED) {
-        if (!final_out && p.arrive) splitk_finish<TN, kThreads>(p, tile, n_base);
-    }
+    if constexpr (FUSE) splitk_finish<TN, kThreads>(p, tile, n_base);
     if constexpr (!GROUPED) break;
     mc += 16 * MT;
     if (mc >= rows) break;
@@ -402,6 +400,13 @@ hipError_t launch_t(const DecodeParams& p, int grid, hipStream_t stream) {
         if (p.log2_fetch > 0) {   // block emulation: fewer steps in flight leave room for the block loop
             hipLaunchKernelGGL((decode_kernel<MT, NS, 2, WAVES, false, true, false>), dim3(grid), dim3(64 * WAVES), 0,
                                stream, p);
+            return hipGetLastError();
+        }
+    }
+    if constexpr (WAVES >= 8 && !GROUPED) {
+        if (p.arrive) {
+            hipLaunchKernelGGL((decode_kernel<MT, NS, U, WAVES, TILE, false, false, false, true>), dim3(grid),
+                               dim3(64 * WAVES), 0, stream, p);
             return hipGetLastError();
         }
     }
@@ -487,7 +492,7 @@ hipError_t launch_decode(const DecodeLaunch& d, hipStream_t stream) {
     const int ns = d.tile_n / 16;
     hipError_t e;
     if (d.L.kind == TL_LAYOUT_KN_ROW)
-        return launch_splitk_reduce(d, launch_kn_decode(p, grid, d.m_tiles16, d.waves, stream), stream);
+        return launch_splitk_reduce(d, launch_kn_decode(p, d.kn_wide, d.kn_wide ? int((d.N + 255) / 256) * d.split_k : grid, d.m_tiles16, d.waves, stream), stream);
     if (d.fp8) return launch_splitk_reduce(d, launch_fp8_decode(p, grid, d.m_tiles16, ns, d.waves, tile, stream), stream);
     switch (d.m_tiles16) {
         case 1: e = launch_m<1>(p, grid, ns, d.waves, tile, grouped, stream); break;

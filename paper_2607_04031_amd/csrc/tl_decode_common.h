@@ -41,7 +41,7 @@ struct DecodeParams {
     int a_rows;              // rows of A; token ids outside [0, a_rows) read zeros
     int total_rows;          // rows of C; group offsets are clamped to [0, total_rows]
     const float* scales;     // FP8 weights: per-output-channel scale [N], or nullptr (1)
-    unsigned* arrive;        // K splits summed inside the launch: one arrival counter per tile, else nullptr
+    unsigned* arrive;        // K splits summed inside the launch (kernels with FUSE): one arrival counter per tile, else nullptr
     int swiglu_up;           // gated grouped launch: row of the first up row (I); C has N = I columns
 };
 
@@ -167,10 +167,11 @@ __device__ inline void splitk_finish(const DecodeParams& p, int tile, int n0) {
 hipError_t launch_fp8_decode(const DecodeParams& p, int grid, int m_tiles16, int ns, int waves, bool tile,
                              hipStream_t stream);
 
-// Decode over a [K][N] row-major weight (tl_decode_kn.hip): 64-column tiles,
-// p.units 64-row K steps split p.split_k ways, 4 or 8 waves; block-granular
-// fetch when p.log2_fetch > 0.
-hipError_t launch_kn_decode(const DecodeParams& p, int grid, int m_tiles16, int waves, hipStream_t stream);
+// Decode over a [K][N] row-major weight (tl_decode_kn.hip): 64-column tiles
+// with 4 or 8 waves, or 256-column ones (wide, M <= 32) with 8, p.units 64-row K
+// steps split p.split_k ways; block-granular fetch (64-column tiles) when
+// p.log2_fetch > 0.
+hipError_t launch_kn_decode(const DecodeParams& p, bool wide, int grid, int m_tiles16, int waves, hipStream_t stream);
 
 // Decode through LDS (tl_decode_lds.hip): 17 <= M <= 64, tile-major,
 // tiles_per_wg 32-row tiles per workgroup (4..7 for M <= 32, 4 above), the

@@ -28,7 +28,7 @@ __device__ inline bf16x8 fp8x8_to_bf16(uint32_t lo, uint32_t hi) {
     return __builtin_bit_cast(bf16x8, r);
 }
 
-template <int MT, int NS, int U, int WAVES, bool TILE>
+template <int MT, int NS, int U, int WAVES, bool TILE, bool FUSE = false>
 __global__ __launch_bounds__(64 * WAVES) void decode_fp8_kernel(DecodeParams p) {
     typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
     constexpr int kWaves = WAVES;
@@ -169,17 +169,23 @@ __global__ __launch_bounds__(64 * WAVES) void decode_fp8_kernel(DecodeParams p) 
             const int m = mt * 16 + (l >> 4) * 4 + r;
             if (m < p.M && n < p.N) {
                 if (final_out) store_out(p.C, int64_t(m) * p.N + n, v[r] * sc, p.out_bf16);
-                else if (p.arrive) store_partial(part + int64_t(m) * p.N + n, v[r] * sc);
+                else if (FUSE) store_partial(part + int64_t(m) * p.N + n, v[r] * sc);
                 else part[int64_t(m) * p.N + n] = v[r] * sc;
             }
         }
     }
-    if (!final_out && p.arrive) splitk_finish<TN, kThreads>(p, tile, n_base);
+    if constexpr (FUSE) splitk_finish<TN, kThreads>(p, tile, n_base);
 }
 
 template <int MT, int NS, int WAVES, bool TILE>
 hipError_t launch_fp8_t(const DecodeParams& p, int grid, hipStream_t stream) {
     constexpr int U = MT >= 2 ? 2 : 4;
+    if constexpr (WAVES >= 8) {
+        if (p.arrive) {
+            hipLaunchKernelGGL((decode_fp8_kernel<MT, NS, U, WAVES, TILE, true>), dim3(grid), dim3(64 * WAVES), 0, stream, p);
+            return hipGetLastError();
+        }
+    }
     hipLaunchKernelGGL((decode_fp8_kernel<MT, NS, U, WAVES, TILE>), dim3(grid), dim3(64 * WAVES), 0, stream, p);
     return hipGetLastError();
 }

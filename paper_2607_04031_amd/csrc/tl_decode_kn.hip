@@ -3,8 +3,15 @@
 //
 // The MFMA operands need eight consecutive k per lane, while a [K][N] weight
 // keeps consecutive n together, so every K step goes through LDS once:
-//   workgroup = 64 output columns (n) x one K split; its waves interleave
-//   along K in 64-row steps.  Per step a wave loads the 64 k-rows x 128 B of
+//   workgroup = 64 NW output columns (n) x one K split; NW waves side by side
+//   take 64 columns each, and WAVES / NW of them interleave along K in 64-row
+//   steps.  NW = 4: a row of the weight is read in 512-byte runs by waves that
+//   stay close together, where workgroups of 64 columns drift apart and ask
+//   for 128 bytes of a row at a time; the reads of one workgroup per CU then
+//   reach 6.2 - 6.6 TB/s instead of 4.4 - 5.3 (M = 8, one MI355X, us: 8192 x
+//   28672 89 -> 76, 57344 x 8192 185 -> 142, 10240 x 8192 33.6 -> 31.3, 8192 x
+//   8192 31.3 -> 27; 2 and 8 columns of waves 79 - 84 and 78 - 98 on the
+//   first).  Per step a wave loads the 64 k-rows x 128 B of
 //   its columns with whole-line loads (instruction i: rows 8 i .. 8 i + 7,
 //   lane l reads 16 bytes of row 8 i + l / 8), writes them to its own LDS
 //   region and reads them back transposed with ds_read_b64_tr_b16 (gfx950):
@@ -25,6 +32,8 @@
 // fp32 partials that the split-K reduce kernel sums in split order.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "tl_decode_common.h"
 
 namespace tl {
@@ -42,12 +51,13 @@ constexpr int kStageBytes = 64 * 128;   // one wave's K step: 64 k-rows x 64 col
 // of each parity.
 __device__ inline int kn_swz(int r, int chunk) { return r * 128 + ((chunk ^ (((r >> 1) & 1) << 1) ^ (((r >> 3) & 1) << 2)) << 4); }
 
-template <int MT, int WAVES, bool BLOCK>
+template <int MT, int WAVES, int NW, bool BLOCK, bool FUSE = false>
 __global__ __launch_bounds__(64 * WAVES) void decode_kn_kernel(DecodeParams p) {
     constexpr int kThreads = 64 * WAVES;
     constexpr int kRedBytes = WAVES * MT * 4 * 64 * 16;
     constexpr int kLds = (WAVES * kStageBytes > kRedBytes) ? WAVES * kStageBytes : kRedBytes;
     static_assert(kLds <= 64 * 1024, "LDS budget");
+    constexpr int KW = WAVES / NW;
     __shared__ __attribute__((aligned(16))) uint8_t smem[kLds];
 
     const int lane = threadIdx.x & 63;
@@ -58,7 +68,8 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kn_kernel(DecodeParams p) {
     const int u1 = int((int64_t(p.units) * (split + 1)) / p.split_k);
     const int st0 = u0 * p.steps_per_unit;
     const int st1 = min(u1 * p.steps_per_unit, p.ksteps);
-    const int n0 = tile * 64;
+    const int nw = wave % NW, kw = wave / NW;
+    const int n0 = (tile * NW + nw) * 64;
 
     // weight loads: lane (lr, lc) reads 16 bytes at column min(n0 + 8 lc, N - 8)
     // of rows k0 + 8 i + lr (N % 8 == 0; columns past N are never stored)
@@ -94,11 +105,17 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kn_kernel(DecodeParams p) {
         aoff[mt] = uint32_t((aok[mt] ? m : 0) * p.K + 8 * g) * 2u;
     }
 
-    f32x4 acc[MT][4];
+    // sums: a wave with a wide tile's fewer K partners walks more steps, so it
+    // keeps odd and even steps (with one M tile also the two halves of a step)
+    // apart -- fp32 chains as short as four or eight K partners give
+    constexpr int SETS = NW == 1 ? 1 : MT == 1 ? 4 : 2;
+    f32x4 acc[SETS][MT][4];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int e = 0; e < SETS; ++e)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[mt][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[e][mt][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const bf16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
 
     i32x4 sink = {0, 0, 0, 0};
@@ -119,8 +136,9 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kn_kernel(DecodeParams p) {
         }
     };
 
-    const int nsteps = st1 - st0 - wave > 0 ? (st1 - st0 - wave + WAVES - 1) / WAVES : 0;
-    int st = st0 + wave;
+    // (a wave whose columns are all past N has none)
+    const int nsteps = n0 < p.N && st1 - st0 - kw > 0 ? (st1 - st0 - kw + KW - 1) / KW : 0;
+    int st = st0 + kw;
     // two steps in flight: the loads of the next step are issued before this
     // step is staged and computed (two register sets, used alternately, so
     // every register index is a compile-time constant)
@@ -139,7 +157,8 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kn_kernel(DecodeParams p) {
     // the wave's staging region as an LDS (address space 3) pointer
     __attribute__((address_space(3))) uint8_t* stage_lds = (__attribute__((address_space(3))) uint8_t*)stage;
     auto lds_ptr = [&](int off) { return (lds_bf16x4*)(stage_lds + off); };
-    auto compute = [&](const bf16x8 (&xw)[8], const bf16x8 (&xa)[MT][2]) {
+    auto compute = [&](const bf16x8 (&xw)[8], const bf16x8 (&xa)[MT][2], auto odd_c) {
+        constexpr int ODD = decltype(odd_c)::value;
 #pragma unroll
         for (int r = 0; r < 8; ++r) *reinterpret_cast<bf16x8*>(stage + wst[r]) = xw[r];
 #pragma unroll
@@ -150,19 +169,21 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kn_kernel(DecodeParams p) {
                 const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(lds_ptr(rtr[h][1][j]));
                 const bf16x8 b = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    acc[mt][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[mt][h], b, acc[mt][j], 0, 0, 0);
+                for (int mt = 0; mt < MT; ++mt) {
+                    f32x4& sum = acc[SETS == 1 ? 0 : SETS == 2 ? ODD : 2 * ODD + h][mt][j];
+                    sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[mt][h], b, sum, 0, 0, 0);
+                }
             }
     };
     bf16x8 xw0[8], xw1[8], xa0[MT][2], xa1[MT][2];
     if (nsteps > 0) gload(st, xw0, xa0);
     for (int i = 0; i < nsteps; i += 2) {
-        if (i + 1 < nsteps) gload(st + WAVES, xw1, xa1);
-        compute(xw0, xa0);
+        if (i + 1 < nsteps) gload(st + KW, xw1, xa1);
+        compute(xw0, xa0, std::integral_constant<int, 0>{});
         if (i + 1 >= nsteps) break;
-        if (i + 2 < nsteps) gload(st + 2 * WAVES, xw0, xa0);
-        compute(xw1, xa1);
-        st += 2 * WAVES;
+        if (i + 2 < nsteps) gload(st + 2 * KW, xw0, xa0);
+        compute(xw1, xa1, std::integral_constant<int, 1>{});
+        st += 2 * KW;
     }
 
     if (p.fetch && lane == 0 && nsteps > 0)
@@ -178,45 +199,63 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kn_kernel(DecodeParams p) {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) red[((wave * MT + mt) * 4 + j) * 64 + lane] = acc[mt][j];
+        for (int j = 0; j < 4; ++j) {
+#pragma unroll
+            for (int e = 1; e < SETS; ++e) acc[0][mt][j] += acc[e][mt][j];
+            red[((wave * MT + mt) * 4 + j) * 64 + lane] = acc[0][mt][j];
+        }
     __syncthreads();
     const bool final_out = p.split_k == 1;
     float* part = p.ws + int64_t(split) * p.ws_stride;
-    for (int e = threadIdx.x; e < MT * 4 * 64; e += kThreads) {
-        const int mt = e / 256, j = (e / 64) % 4, l = e % 64;
-        f32x4 v = red[(mt * 4 + j) * 64 + l];
+    for (int e = threadIdx.x; e < NW * MT * 4 * 64; e += kThreads) {
+        const int l = e % 64, j = (e / 64) % (4 * NW), mt = e / (256 * NW);
+        const f32x4* first = red + ((j / 4 * MT + mt) * 4 + j % 4) * 64 + l;
+        f32x4 v = *first;
 #pragma unroll
-        for (int w = 1; w < WAVES; ++w) v += red[((w * MT + mt) * 4 + j) * 64 + l];
-        const int n = n0 + j * 16 + (l & 15);
+        for (int w = 1; w < KW; ++w) v += first[w * NW * MT * 256];
+        const int n = (tile * NW * 4 + j) * 16 + (l & 15);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int m = mt * 16 + (l >> 4) * 4 + r;
             if (m < p.M && n < p.N) {
                 if (final_out) store_out(p.C, int64_t(m) * p.N + n, v[r], p.out_bf16);
-                else if (p.arrive) store_partial(part + int64_t(m) * p.N + n, v[r]);
+                else if (FUSE) store_partial(part + int64_t(m) * p.N + n, v[r]);
                 else part[int64_t(m) * p.N + n] = v[r];
             }
         }
     }
-    if (!final_out && p.arrive) splitk_finish<64, kThreads>(p, tile, n0);
+    if constexpr (FUSE) splitk_finish<64 * NW, kThreads>(p, tile, tile * NW * 64);
 }
 
-template <int MT, int WAVES>
+template <int MT, int WAVES, int NW>
 hipError_t launch_kn_w(const DecodeParams& p, int grid, hipStream_t stream) {
-    if (p.log2_fetch > 0)
-        hipLaunchKernelGGL((decode_kn_kernel<MT, WAVES, true>), dim3(grid), dim3(64 * WAVES), 0, stream, p);
-    else
-        hipLaunchKernelGGL((decode_kn_kernel<MT, WAVES, false>), dim3(grid), dim3(64 * WAVES), 0, stream, p);
+    if constexpr (NW == 1 && WAVES == 8) {
+        if (p.arrive) {
+            hipLaunchKernelGGL((decode_kn_kernel<MT, 8, 1, false, true>), dim3(grid), dim3(512), 0, stream, p);
+            return hipGetLastError();
+        }
+    }
+    if constexpr (NW == 1) {
+        if (p.log2_fetch > 0) {
+            hipLaunchKernelGGL((decode_kn_kernel<MT, WAVES, 1, true>), dim3(grid), dim3(64 * WAVES), 0, stream, p);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((decode_kn_kernel<MT, WAVES, NW, false>), dim3(grid), dim3(64 * WAVES), 0, stream, p);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_kn_decode(const DecodeParams& p, int grid, int m_tiles16, int waves, hipStream_t stream) {
+hipError_t launch_kn_decode(const DecodeParams& p, bool wide, int grid, int m_tiles16, int waves, hipStream_t stream) {
+    if (wide) {
+        if (m_tiles16 > 2 || p.log2_fetch > 0) return hipErrorInvalidValue;
+        return m_tiles16 == 1 ? launch_kn_w<1, 8, 4>(p, grid, stream) : launch_kn_w<2, 8, 4>(p, grid, stream);
+    }
     switch (m_tiles16) {
-        case 1: return waves == 8 ? launch_kn_w<1, 8>(p, grid, stream) : launch_kn_w<1, 4>(p, grid, stream);
-        case 2: return waves == 8 ? launch_kn_w<2, 8>(p, grid, stream) : launch_kn_w<2, 4>(p, grid, stream);
-        default: return launch_kn_w<4, 4>(p, grid, stream);
+        case 1: return waves == 8 ? launch_kn_w<1, 8, 1>(p, grid, stream) : launch_kn_w<1, 4, 1>(p, grid, stream);
+        case 2: return waves == 8 ? launch_kn_w<2, 8, 1>(p, grid, stream) : launch_kn_w<2, 4, 1>(p, grid, stream);
+        default: return launch_kn_w<4, 4, 1>(p, grid, stream);
     }
 }
 

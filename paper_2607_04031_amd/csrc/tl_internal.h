@@ -80,6 +80,7 @@ struct DecodeLaunch {
     // FP8 (E4M3) weight, bf16 activations; optional per-output-channel scales [N]
     bool fp8 = false;
     const float* scales = nullptr;
+    bool kn_wide = false;       // [K][N] weight: 256-column tiles (M <= 32)
     // > 0: the LDS kernel with this many 32-row tiles per workgroup (17 <= M <= 64, tile-major, N % (32 lds_tiles) == 0, K % 512 == 0)
     int lds_tiles = 0;
 };

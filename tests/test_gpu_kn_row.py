@@ -71,6 +71,21 @@ def test_kn_row_exact_inputs_bit_exact(M, N, K, S):
     assert np.array_equal(C1, C2)
 
 
+# 256-column workgroups: a last one with columns past N (whole 64-column waves
+# and part of one), K steps fewer than the wave pairs, sixteen splits, three
+# splits of rows that are not whole lines, more tiles than CUs, M to 32
+@pytest.mark.parametrize("M,N,K", [(8, 2824, 16384), (32, 2816, 16384), (5, 45000, 64), (16, 43576, 192),
+                                   (17, 33096, 3072), (1, 98312, 128)])
+def test_kn_row_wide_workgroups(M, N, K):
+    banner(f"KN_ROW 256-column workgroups M={M} N={N} K={K}")
+    A = synth.normal_bf16((M, K), seed=1350 + M)
+    W = synth.normal_bf16((N, K), seed=1351, sigma=synth.W_SIGMA)
+    tl.tl_fetch_counter_read()
+    got = run_kn(A, W, tl.layout(kind=KN), fetch=tl.TL_FETCH_NATIVE | tl.TL_FETCH_COUNT)
+    assert tl.tl_fetch_counter_read() == -(-N // 64) * 64 * K * 2       # the 64-column tiles inside N
+    parity(host_f32(got), oracle.gemm_f64(A, W), f"KN_ROW M={M} N={N} K={K}")
+
+
 def test_kn_row_one_hot_rows():
     """A[m] = e_{k_m}: C[m][n] = W[n][k_m] exactly -- pins which stored element
     the transposed reads deliver to which (m, n)."""
