@@ -25,7 +25,8 @@
 //   whole 128-byte lines (see decode_kernel).
 // Reduction
 //   waves -> LDS -> fixed-order sum; K-splits -> fp32 partials in a workspace,
-//   summed in split order by a second small kernel.  No float atomics, so
+//   summed in split order by a second small kernel, or on small weights
+//   (FUSE) by the last workgroup of the tile to arrive.  No float atomics, so
 //   results are bitwise reproducible.
 #include <hip/hip_runtime.h>
 

@@ -28,8 +28,16 @@ __device__ inline bf16x8 fp8x8_to_bf16(uint32_t lo, uint32_t hi) {
     return __builtin_bit_cast(bf16x8, r);
 }
 
+// One M tile on tile-major weights: at most 128 registers (row addresses as
+// 32-bit offsets), so four waves fit a SIMD where three did -- two 8-wave or
+// four 4-wave workgroups per CU, one round for the planner's 257 - 512 and 769
+// - 1024 workgroups.  M = 16, one MI355X, us: 10240 x 8192 (480 workgroups)
+// 20.4 -> 18.9, 28672 x 4096 (448) 24.1 -> 22.1, 57344 x 8192 (896) 78.8 ->
+// 76.3; 8192 x 8192 (256) 15.9 -> 15.5.  Row-major weights spill at 128
+// registers (each subtile's rows have their own stride arithmetic) and keep three.
 template <int MT, int NS, int U, int WAVES, bool TILE, bool FUSE = false>
-__global__ __launch_bounds__(64 * WAVES) void decode_fp8_kernel(DecodeParams p) {
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(MT == 1 && TILE ? 4 : 1)))
+void decode_fp8_kernel(DecodeParams p) {
     typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
     constexpr int kWaves = WAVES;
     constexpr int kThreads = 64 * WAVES;
@@ -46,21 +54,26 @@ __global__ __launch_bounds__(64 * WAVES) void decode_fp8_kernel(DecodeParams p) 
     const int n_base = tile * TN;
     const int g = lane >> 4, q = lane & 15;
     const int kg = g * 16;                     // this lane's 16 K values of a step
-    const uint8_t* wrow[NS];
+    // the tile's first row as a uniform base, rows as 32-bit offsets (a tile's
+    // rows and the activations span less than 2^31 bytes, as the planner checks)
+    auto row_off = [&](int n) -> int64_t {
+        return TILE ? int64_t(n >> p.log2_br) * p.strip_bytes + (int64_t(n & ((1 << p.log2_br) - 1)) << p.log2_bc)
+                    : int64_t(n) * p.K;
+    };
+    const int64_t tile_off = row_off(n_base);
+    const uint8_t* wtile = p.W + tile_off;
+    uint32_t wrow[NS];
 #pragma unroll
-    for (int j = 0; j < NS; ++j) {
-        const int n = min(n_base + j * 16 + q, p.N - 1);
-        wrow[j] = p.W + (TILE ? int64_t(n >> p.log2_br) * p.strip_bytes + (int64_t(n & ((1 << p.log2_br) - 1)) << p.log2_bc)
-                              : int64_t(n) * p.K);
-    }
-    const uint16_t* arow[MT];
+    for (int j = 0; j < NS; ++j) wrow[j] = uint32_t(row_off(min(n_base + j * 16 + q, p.N - 1)) - tile_off);
+    const uint8_t* Ab = reinterpret_cast<const uint8_t*>(p.A);
+    uint32_t arow[MT];
     bool aok[MT], aany[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
         const int m = mt * 16 + q;
         aok[mt] = m < p.M;
         aany[mt] = mt * 16 < p.M;
-        arow[mt] = p.A + int64_t(aok[mt] ? m : 0) * p.K + kg;
+        arow[mt] = uint32_t((aok[mt] ? m : 0) * p.K + kg) * 2u;
     }
     f32x4 acc[MT][NS];
 #pragma unroll
@@ -71,19 +84,19 @@ __global__ __launch_bounds__(64 * WAVES) void decode_fp8_kernel(DecodeParams p) 
     const int nsteps = st1f - st0 - wave > 0 ? (st1f - st0 - wave + kWaves - 1) / kWaves : 0;
     int st = st0 + wave;
     int i = 0;
-    auto koff = [&](int k) -> int64_t {
-        if (TILE) return (int64_t(k >> p.log2_bc) << p.log2_G) + int64_t(k & p.bc_mask);
-        return int64_t(k);
+    auto koff = [&](int k) -> uint32_t {
+        if (TILE) return (uint32_t(k >> p.log2_bc) << p.log2_G) + uint32_t(k & p.bc_mask);
+        return uint32_t(k);
     };
     auto load = [&](int k, u32x4v (&x)[NS], bf16x8 (&a)[MT][2]) {
-        const int64_t ko = koff(k + kg);
+        const uint32_t ko = koff(k + kg);
 #pragma unroll
-        for (int j = 0; j < NS; ++j) x[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4v*>(wrow[j] + ko));
+        for (int j = 0; j < NS; ++j) x[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4v*>(wtile + (wrow[j] + ko)));
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             if (aany[mt]) {
-                a[mt][0] = aok[mt] ? *reinterpret_cast<const bf16x8*>(arow[mt] + k) : zero8;
-                a[mt][1] = aok[mt] ? *reinterpret_cast<const bf16x8*>(arow[mt] + k + 8) : zero8;
+                a[mt][0] = aok[mt] ? *reinterpret_cast<const bf16x8*>(Ab + (arow[mt] + uint32_t(k) * 2u)) : zero8;
+                a[mt][1] = aok[mt] ? *reinterpret_cast<const bf16x8*>(Ab + (arow[mt] + uint32_t(k) * 2u) + 16) : zero8;
             } else {
                 a[mt][0] = zero8;
                 a[mt][1] = zero8;
@@ -126,17 +139,17 @@ __global__ __launch_bounds__(64 * WAVES) void decode_fp8_kernel(DecodeParams p) 
         const bool kin = k + kg < p.K;
         u32x4v x[NS];
         bf16x8 a[MT][2];
-        const int64_t ko = koff(kin ? k + kg : 0);
+        const uint32_t ko = koff(kin ? k + kg : 0);
 #pragma unroll
         for (int j = 0; j < NS; ++j) {
-            const u32x4v v = __builtin_nontemporal_load(reinterpret_cast<const u32x4v*>(wrow[j] + ko));
+            const u32x4v v = __builtin_nontemporal_load(reinterpret_cast<const u32x4v*>(wtile + (wrow[j] + ko)));
             x[j] = kin ? v : u32x4v{0u, 0u, 0u, 0u};
         }
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-            const uint16_t* pa = kin ? arow[mt] + k : arow[mt] - kg;
+            const uint8_t* pa = Ab + (kin ? arow[mt] + uint32_t(k) * 2u : arow[mt] - uint32_t(kg) * 2u);
             const bf16x8 v0 = *reinterpret_cast<const bf16x8*>(pa);
-            const bf16x8 v1 = *reinterpret_cast<const bf16x8*>(pa + 8);
+            const bf16x8 v1 = *reinterpret_cast<const bf16x8*>(pa + 16);
             a[mt][0] = kin && aok[mt] ? v0 : zero8;
             a[mt][1] = kin && aok[mt] ? v1 : zero8;
         }
