@@ -70,12 +70,6 @@ struct StateRef {
     unsigned* arrive = nullptr;
 };
 
-// tiles with a counter (64 bytes apart: 16 words); launches with more K-split
-// tiles, and tl_gemm_noalloc, sum their partials in a second launch
-constexpr int kArriveTiles = 2048;
-constexpr int kArriveAt = 8;              // in 8-byte words from the tally
-constexpr int kStateWords = kArriveAt + kArriveTiles * 8;
-
 std::mutex g_mu;
 std::map<std::pair<int, void*>, std::shared_ptr<StreamState>> g_state;
 
@@ -99,7 +93,7 @@ int get_state(hipStream_t stream, size_t ws_bytes, StateRef* out) {
     StreamState& st = *sp;
     if (!st.fetch) {
         if (hipMalloc(&st.fetch, kStateWords * sizeof(unsigned long long)) != hipSuccess) { st.fetch = nullptr; return TL_ENOMEM; }
-        if (launch_zero_u64(st.fetch, kStateWords, stream) != hipSuccess) {   // the next call allocates and clears again
+        if (launch_zero_u64(st.fetch, stream) != hipSuccess) {   // the next call allocates and clears again
             (void)hipFree(st.fetch);
             st.fetch = nullptr;
             return TL_EHIP;
@@ -863,15 +857,16 @@ static int gemm_impl(const void* A, const void* W, const float* scales, void* C,
         m.ws = st.ws;
         m.ws_stride = (M * N + 3) / 4 * 4;
         m.w_once = true;
-        e = launch_medium(m, int(p.pub.workgroups), p.medium_cfg, layout->kind == TL_LAYOUT_TILE, false, s);
+        const MediumLaunch ml{m, int(p.pub.workgroups), p.medium_cfg, layout->kind == TL_LAYOUT_TILE, false};
         DecodeLaunch r;
+        r.medium = &ml;
         r.C = C;
         r.ws = st.ws;
         r.M = M;
         r.N = N;
         r.split_k = p.pub.split_k;
         r.out_bf16 = p.out_bf16;
-        e = launch_splitk_reduce(r, e, s);
+        e = launch_decode(r, s);
     } else if (p.pub.kernel == 1) {
         DecodeLaunch d;
         d.A = static_cast<const uint16_t*>(A);
@@ -988,7 +983,11 @@ static int grouped_impl(const void* A, int64_t a_rows, const int32_t* token_ids,
         m.total_rows = int(total_rows);
         m.w_once = max_group_rows <= medium_tile_m(cfg);
         const bool tile = layout->kind == TL_LAYOUT_TILE;
-        return launch_medium(m, int(grid), cfg, tile, swiglu, s) == hipSuccess ? TL_OK : TL_EHIP;
+        const MediumLaunch ml{m, int(grid), cfg, tile, swiglu};
+        DecodeLaunch r;
+        r.medium = &ml;
+        r.split_k = 1;
+        return launch_decode(r, s) == hipSuccess ? TL_OK : TL_EHIP;
     }
     DecodeLaunch d;
     d.A = static_cast<const uint16_t*>(A);
@@ -1167,7 +1166,7 @@ int tl_fetch_counter_read(void* stream, int64_t* bytes) {
     unsigned long long v = 0;
     if (hipStreamSynchronize(s) != hipSuccess) return TL_EHIP;
     if (hipMemcpy(&v, st.fetch, sizeof v, hipMemcpyDeviceToHost) != hipSuccess) return TL_EHIP;
-    if (launch_zero_u64(st.fetch, 1, s) != hipSuccess) return TL_EHIP;
+    if (launch_zero_u64(st.fetch, s) != hipSuccess) return TL_EHIP;
     if (hipStreamSynchronize(s) != hipSuccess) return TL_EHIP;
     *bytes = int64_t(v);
     return TL_OK;

@@ -34,6 +34,7 @@
 #include <cstring>
 
 #include "tl_decode_common.h"
+#include "tl_medium.h"
 
 namespace tl {
 namespace {
@@ -381,8 +382,8 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* ws, voi
     }
 }
 
-__global__ void zero_u64_kernel(unsigned long long* p, int n) {
-    for (int i = threadIdx.x; i < n; i += 256) p[i] = 0ull;
+__global__ void zero_u64_kernel(unsigned long long* p) {
+    for (int i = threadIdx.x; i < kStateWords; i += 1024) p[i] = 0ull;
 }
 
 template <int MT, int NS, int WAVES, bool TILE, bool GROUPED, bool SWIGLU = false>
@@ -444,12 +445,15 @@ hipError_t launch_m(const DecodeParams& p, int grid, int ns, int waves, bool til
 
 }  // namespace
 
-hipError_t launch_zero_u64(unsigned long long* p, int n, hipStream_t stream) {
-    hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(256), 0, stream, p, n);
+hipError_t launch_zero_u64(unsigned long long* p, hipStream_t stream) {
+    hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(1024), 0, stream, p);
     return hipGetLastError();
 }
 
 hipError_t launch_decode(const DecodeLaunch& d, hipStream_t stream) {
+    if (d.medium)
+        return launch_splitk_reduce(
+            d, launch_medium(d.medium->p, d.medium->grid, d.medium->cfg, d.medium->tile, d.medium->swiglu, stream), stream);
     DecodeParams p;
     p.A = d.A;
     p.W = d.W;

@@ -49,6 +49,8 @@ inline int64_t packed_bytes(const Layout& L, int64_t rows, int64_t cols) {
 hipError_t launch_repack(const void* src, void* dst, int64_t rows, int64_t cols,
                          const Layout& L, bool inverse, hipStream_t stream);
 
+struct MediumLaunch;
+
 struct DecodeLaunch {
     const uint16_t* A;
     const uint8_t* W;
@@ -80,6 +82,7 @@ struct DecodeLaunch {
     // FP8 (E4M3) weight, bf16 activations; optional per-output-channel scales [N]
     bool fp8 = false;
     const float* scales = nullptr;
+    const MediumLaunch* medium = nullptr;   // a launch of the row-adaptive kernel (the K-split fields apply to its reduce)
     bool kn_wide = false;       // [K][N] weight: 256-column tiles (M <= 32)
     // > 0: the LDS kernel with this many 32-row tiles per workgroup (17 <= M <= 64, tile-major, N % (32 lds_tiles) == 0, K % 512 == 0)
     int lds_tiles = 0;
@@ -88,7 +91,13 @@ struct DecodeLaunch {
 hipError_t launch_decode(const DecodeLaunch& d, hipStream_t stream);
 // *p = 0, enqueued on 'stream' as a one-thread kernel (not a memset node, so
 // the clear behaves like any kernel inside a captured graph)
-hipError_t launch_zero_u64(unsigned long long* p, int n, hipStream_t stream);
+// a stream's device state: the fetch tally, then (kArriveAt words on) the
+// arrival counters of kArriveTiles tiles, 64 bytes apart, which are zero
+// between calls; launch_zero_u64 clears all of it
+constexpr int kArriveTiles = 2048;
+constexpr int kArriveAt = 8;
+constexpr int kStateWords = kArriveAt + kArriveTiles * 8;
+hipError_t launch_zero_u64(unsigned long long* p, hipStream_t stream);
 // the fixed-order split-K reduce that follows a decode launch with split_k > 1
 // (passes 'e' through when it is an error or split_k is 1)
 hipError_t launch_splitk_reduce(const DecodeLaunch& d, hipError_t e, hipStream_t stream);

@@ -45,6 +45,14 @@ enum class MediumConfig {
 inline int medium_tile_m(MediumConfig c) { return c == MediumConfig::kWide ? 256 : c == MediumConfig::kPair192 ? 192 : 128; }
 inline int medium_tile_n(MediumConfig c) { return c == MediumConfig::kWide ? 256 : 128; }
 
+// One launch (by launch_decode, with DecodeLaunch::medium).
+struct MediumLaunch {
+    MediumParams p;
+    int grid;
+    MediumConfig cfg;
+    bool tile, swiglu;
+};
+
 hipError_t launch_medium(const MediumParams& p, int grid, MediumConfig cfg, bool tile, bool swiglu, hipStream_t stream);
 
 }  // namespace tl
