@@ -294,15 +294,17 @@ int tl_gemm_plan(int64_t M, int64_t N, int64_t K, const tl_layout_desc* layout,
  * max_group_rows: host bound on the rows of one group; it picks the kernel and
  *                its M tile: the decode kernel with 16 rows up to 16 (32 or 64
  *                where a tile is requested), above that the row-adaptive
- *                kernel with up to 256 rows.  A group with more rows is
+ *                kernel with up to 192 rows.  A group with more rows is
  *                processed in several passes over its weight (correct, more
- *                traffic).
+ *                traffic).  Results do not depend on it.
  * W:             device, group_stride bytes apart (a multiple of 16, at least
  *                one weight: tl_tile_bytes for tile-major, N * K * 2 else).
  * C:             device [total_rows][N] row-major, fp32 or bf16 per
  *                layout->out_dtype; rows of empty groups are not written.
  * Weights stream once per group and pass (one workgroup per group, row pass
- * and tile of weight rows, K not split), so results match tl_gemm to rounding.
+ * and tile of weight rows, K not split), so results match tl_gemm to rounding;
+ * a row's bits depend on its activations and its group's weight only, not on
+ * the other rows or the kernel.
  * fetch_mode: as tl_gemm (TL_FETCH_BLOCK on NK_ROW is not supported here).
  * Errors: TL_EINVAL for num_groups < 1, total_rows < 0, a_rows < 1, rows
  * beyond 2^31 - 1, a short or misaligned group_stride, NULL or misaligned

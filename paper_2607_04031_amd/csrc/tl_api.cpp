@@ -170,7 +170,7 @@ struct Plan {
     int split_rest = 0;          // prefill: K splits of the 256 x 256 tiles past n_main (0: 128 x 128 tiles)
     bool persist = false;        // prefill: one workgroup per CU walks the main launch's tiles
     bool medium = false;         // all rows in one tile of the row-adaptive kernel
-    MediumConfig medium_cfg = MediumConfig::kPair128;
+    MediumConfig medium_cfg = MediumConfig::kNarrow;
 };
 
 constexpr int kDecodeMaxM = 64;
@@ -691,7 +691,7 @@ int plan_gemm(int64_t M, int64_t N, int64_t K, const tl_layout_desc* d, int32_t 
         if (!d->tile_m && !d->tile_n && M <= kMediumMaxM && !p.block_row && !p.split_rest &&
             mt == 1 && p.n_main == N) {
             p.medium = true;
-            p.medium_cfg = tn == 256 ? MediumConfig::kWide : MediumConfig::kPair128;
+            p.medium_cfg = tn == 256 ? MediumConfig::kWide : MediumConfig::kNarrow;
             p.persist = false;
             p.pub.waves = tn == 256 ? 8 : 4;
         }
@@ -755,30 +755,27 @@ MediumParams medium_params(const Plan& p, const void* A, const void* W, void* C,
 // Whether a grouped launch takes the row-adaptive kernel, its configuration
 // and its grid.  It does when a group may exceed one 16-row MFMA tile of the
 // decode kernel (which streams a group's weight once per 64 rows and reloads
-// the activations for every 64 weight rows) and no tile is requested:
-// measured over 60 shapes of 16 - 128 experts, groups of up to 17 - 552 rows
-// run 1.0 - 4.2x faster, and at up to 16 rows the two are equal (within 3 %),
-// where the decode kernel stays.  Configurations, both sides from that sweep:
-//  - 256 x 256 tiles, one workgroup per CU, up to 256 rows: fewest activation
-//    loads (128 experts of 128 rows, K = 2048: 271 us for both projections
-//    against 288 with 192-row tiles);
-//  - 128 x 128 tiles, two per CU, when the wide tiles are too few to keep HBM
-//    busy: under 192 of them, or under 128 for groups past 64 rows, whose
-//    MFMA work weighs more (16 experts of 27 rows 38.8 -> 31.9 us; 144 wide
-//    tiles of 147 rows 59.6 us against 78.2);
-//  - 192 x 128 tiles, two per CU, past 256 rows, where a group is cut into
-//    chunks anyway (16 groups of 276: 119 -> 81 us).
+// the activations for every 64 weight rows) and no tile is requested: groups
+// of 17 - 1024 rows (1 - 300 groups) run 1.1 - 8x faster, bit for bit the same
+// results; at up to 16 rows the two are equal (within 3 %), where the decode
+// kernel stays.  Configurations, both projections at K = 4096 / 2048 (8 groups
+// is 128 wide tiles per projection, 9 is 144), us, 192 x 256 / 128 x 128:
+//  - 192 x 256 tiles, one workgroup per CU, where there are more than half as
+//    many of them as CUs: fewest activation loads, and a group's weight is read
+//    by one workgroup up to 192 rows (9 groups of 30 / 100 / 150 rows: 84 /
+//    107 / 120 against 93 / 118 / 177; 128 of 128: 265 against 325);
+//  - 128 x 128 tiles, two per CU, for fewer, which would leave the CUs idle (8
+//    groups of 64 rows: 69 against 86; of 130: 115 against 120).
 bool medium_grouped(const Plan& p, const tl_layout_desc* d, int64_t num_groups, int64_t total_rows,
                     int64_t max_group_rows, int64_t N, int64_t K, bool swiglu, MediumConfig* cfg, int64_t* grid) {
     if (max_group_rows <= 16 || total_rows >= (int64_t(1) << 30) || d->tile_m || d->tile_n || d->tile_k) return false;
     const int64_t kp = p.L.kind == TL_LAYOUT_TILE ? padded_cols(p.L, K) : K;
     if (256 * kp * 2 >= (int64_t(1) << 32)) return false;   // 32-bit offsets inside a tile's weight rows
     const int64_t groups = std::min(num_groups, total_rows);
-    const int64_t wide_cols = medium_tile_n(MediumConfig::kWide) / (swiglu ? 2 : 1);
-    const int64_t wide = groups * ((N + wide_cols - 1) / wide_cols);
-    if (max_group_rows > 256) *cfg = MediumConfig::kPair192;
-    else if (wide >= (max_group_rows <= 64 ? 192 : 128)) *cfg = MediumConfig::kWide;
-    else *cfg = MediumConfig::kPair128;
+    const int64_t wide_cols = medium_tile_n(MediumConfig::kGroupWide) / (swiglu ? 2 : 1);
+    const int64_t wide_rows = medium_tile_m(MediumConfig::kGroupWide) * groups;   // (of groups alike)
+    const int64_t wide = groups * ((total_rows + wide_rows - 1) / wide_rows) * ((N + wide_cols - 1) / wide_cols);
+    *cfg = 2 * wide > kCUs ? MediumConfig::kGroupWide : MediumConfig::kGroupNarrow;
     // at most total_rows / tile_m whole chunks and one more per group; the
     // kernel finds each workgroup's group and rows from the device offsets
     const int64_t cols = medium_tile_n(*cfg) / (swiglu ? 2 : 1);
@@ -856,7 +853,6 @@ static int gemm_impl(const void* A, const void* W, const float* scales, void* C,
         m.split_k = p.pub.split_k;
         m.ws = st.ws;
         m.ws_stride = (M * N + 3) / 4 * 4;
-        m.w_once = true;
         const MediumLaunch ml{m, int(p.pub.workgroups), p.medium_cfg, layout->kind == TL_LAYOUT_TILE, false};
         DecodeLaunch r;
         r.medium = &ml;
@@ -981,7 +977,6 @@ static int grouped_impl(const void* A, int64_t a_rows, const int32_t* token_ids,
         m.group_stride = group_stride;
         m.a_rows = int(a_rows);
         m.total_rows = int(total_rows);
-        m.w_once = max_group_rows <= medium_tile_m(cfg);
         const bool tile = layout->kind == TL_LAYOUT_TILE;
         const MediumLaunch ml{m, int(grid), cfg, tile, swiglu};
         DecodeLaunch r;

@@ -20,7 +20,6 @@ struct MediumParams {
     int log2_br = 0, log2_bc = 0, log2_G = 0;
     int bc_mask = 0;
     bool out_bf16 = false;
-    bool w_once = false;     // one workgroup reads a weight byte (row chunks do not share it): non-temporal loads
     int n_tiles = 0;         // column tiles
     // one weight (num_groups 0): total_rows rows in one tile, K split split_k
     // ways (> 1: fp32 partials at ws, ws_stride floats apart)
@@ -36,14 +35,16 @@ struct MediumParams {
     int total_rows = 0;
 };
 
-// Tiles of C (rows x columns) and what a CU holds of them.
+// Tiles of C (rows x columns) and what a CU holds of them; three weight
+// stages, one (256 columns) or two (128) workgroups per CU.
 enum class MediumConfig {
-    kWide,      // 256 x 256, 8 waves, three weight stages, one workgroup per CU
-    kPair192,   // 192 x 128, 4 waves, two weight stages, two workgroups per CU
-    kPair128    // 128 x 128, 4 waves, three weight stages, two workgroups per CU
+    kWide,         // one weight: 256 x 256, 8 waves
+    kNarrow,       // one weight: 128 x 128, 4 waves
+    kGroupWide,    // groups: 192 x 256, 8 waves
+    kGroupNarrow   // groups: 128 x 128, 4 waves
 };
-inline int medium_tile_m(MediumConfig c) { return c == MediumConfig::kWide ? 256 : c == MediumConfig::kPair192 ? 192 : 128; }
-inline int medium_tile_n(MediumConfig c) { return c == MediumConfig::kWide ? 256 : 128; }
+inline int medium_tile_m(MediumConfig c) { return c == MediumConfig::kWide ? 256 : c == MediumConfig::kGroupWide ? 192 : 128; }
+inline int medium_tile_n(MediumConfig c) { return c == MediumConfig::kWide || c == MediumConfig::kGroupWide ? 256 : 128; }
 
 // One launch (by launch_decode, with DecodeLaunch::medium).
 struct MediumLaunch {
