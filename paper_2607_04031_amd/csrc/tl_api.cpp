@@ -435,12 +435,14 @@ int plan_gemm(int64_t M, int64_t N, int64_t K, const tl_layout_desc* d, int32_t 
         // M = 32: 28.7 us streaming).  QKV at M = 32, whose streaming plan
         // needs 1120 workgroups, 43.0 -> 31.5 us, down 84.1 -> 72.1, gate+up
         // 181 -> 137
+        // (its lanes' weight offsets are 32-bit over the T tiles)
+        auto lds_fits = [&](int64_t T) { return 32 * T * kp * s < (int64_t(1) << 32); };
         if (tile && !p.fp8 && p.m_tiles16 == 2 && !d->tile_n && !d->split_k && N % 32 == 0 && K % 512 == 0 &&
             p.L.br <= 32 && 512 % p.k_unit == 0) {
             const int64_t strips = N / 32, chunks = K / 512;
             bool found = false;   // the first whole-round (T, S) decides
             for (int T = 7; T >= 4 && !found; --T) {
-                if (strips % T) continue;
+                if (strips % T || !lds_fits(T)) continue;
                 for (int64_t s2 = 1; s2 <= 8 && chunks / s2 >= 4 && !found; s2 *= 2) {
                     const int64_t w = strips / T * s2;
                     if (w % kCUs == 0 && w <= 4 * kCUs) {
@@ -472,7 +474,7 @@ int plan_gemm(int64_t M, int64_t N, int64_t K, const tl_layout_desc* d, int32_t 
             int64_t s_fit = groups >= kCUs ? 1 : 0;
             for (int64_t s2 = 1; s2 <= 8 && chunks / s2 >= 4 && groups < kCUs; ++s2)
                 if (groups * s2 <= kCUs) s_fit = s2;
-            if (s_fit && 8 * groups * s_fit >= 7 * kCUs) {
+            if (s_fit && 8 * groups * s_fit >= 7 * kCUs && lds_fits(4)) {
                 p.lds_tiles = 4;
                 S = s_fit;
                 tn = 32;

@@ -85,7 +85,7 @@ __global__ __launch_bounds__(kLdsThreads) void decode_lds_kernel(DecodeParams p)
     // operand read fall in distinct banks.  Rows of A past M repeat row M - 1
     // (their sums are never stored).
     const int lrow = lane >> 3, lpos = lane & 7;
-    uint32_t off[LPW];
+    uint32_t off[LPW];                                    // (the planner keeps 32 T weight rows below 4 GB)
 #pragma unroll
     for (int i = 0; i < LPW; ++i) {
         const int ld = wave + kLdsWaves * i, r = 8 * ld + lrow;
