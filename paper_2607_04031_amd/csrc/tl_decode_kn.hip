@@ -55,9 +55,12 @@ template <int MT, int WAVES, int NW, bool BLOCK, bool FUSE = false>
 __global__ __launch_bounds__(64 * WAVES) void decode_kn_kernel(DecodeParams p) {
     constexpr int kThreads = 64 * WAVES;
     constexpr int kRedBytes = WAVES * MT * 4 * 64 * 16;
-    constexpr int kLds = (WAVES * kStageBytes > kRedBytes) ? WAVES * kStageBytes : kRedBytes;
-    static_assert(kLds <= 64 * 1024, "LDS budget");
+    constexpr bool LONG = NW > 1 && MT > 1;      // the sums have LDS of their own, past the staging
+    constexpr int kRedAt = LONG ? WAVES * kStageBytes : 0;
+    constexpr int kLds = kRedAt + (WAVES * kStageBytes > kRedBytes ? WAVES * kStageBytes : kRedBytes);
+    static_assert(kLds <= (LONG ? 128 : 64) * 1024, "LDS budget");
     constexpr int KW = WAVES / NW;
+    constexpr int SETS = NW > 1 && !LONG ? 4 : 1;
     __shared__ __attribute__((aligned(16))) uint8_t smem[kLds];
 
     const int lane = threadIdx.x & 63;
@@ -106,9 +109,13 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kn_kernel(DecodeParams p) {
     }
 
     // sums: a wave with a wide tile's fewer K partners walks more steps, so it
-    // keeps odd and even steps (with one M tile also the two halves of a step)
-    // apart -- fp32 chains as short as four or eight K partners give
-    constexpr int SETS = NW == 1 ? 1 : MT == 1 ? 4 : 2;
+    // keeps four chains -- together at least as many as four K partners have in
+    // the 64-column plan's splits, of which there are up to twice as many.  One
+    // M tile: odd and even steps and the two halves of a step apart, in
+    // registers.  Two M tiles (LONG), which leave none for them (256 and
+    // spills): one chain after the other, added up in LDS.  M = 32, fp32 out,
+    // 24576 x 4096: 1.03e-7 from the exact sums (1.14e-7 on 64 columns, 1.34e-7
+    // with two chains) in 46.0 us (51.2; 45.3)
     f32x4 acc[SETS][MT][4];
 #pragma unroll
     for (int e = 0; e < SETS; ++e)
@@ -170,13 +177,20 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kn_kernel(DecodeParams p) {
                 const bf16x8 b = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt) {
-                    f32x4& sum = acc[SETS == 1 ? 0 : SETS == 2 ? ODD : 2 * ODD + h][mt][j];
+                    f32x4& sum = acc[SETS == 1 ? 0 : 2 * ODD + h][mt][j];
                     sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[mt][h], b, sum, 0, 0, 0);
                 }
             }
     };
+    f32x4* red = reinterpret_cast<f32x4*>(smem + kRedAt);        // [WAVES][MT][4][64]
+    if constexpr (LONG) {
+#pragma unroll
+        for (int e = 0; e < MT * 4; ++e) red[(wave * MT * 4 + e) * 64 + lane] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     bf16x8 xw0[8], xw1[8], xa0[MT][2], xa1[MT][2];
     if (nsteps > 0) gload(st, xw0, xa0);
+    [[maybe_unused]] const int chain = (nsteps + 7) / 8 * 2;     // LONG: steps of one of the four chains
+    [[maybe_unused]] int left = chain;
     for (int i = 0; i < nsteps; i += 2) {
         if (i + 1 < nsteps) gload(st + KW, xw1, xa1);
         compute(xw0, xa0, std::integral_constant<int, 0>{});
@@ -184,6 +198,18 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kn_kernel(DecodeParams p) {
         if (i + 2 < nsteps) gload(st + 2 * KW, xw0, xa0);
         compute(xw1, xa1, std::integral_constant<int, 1>{});
         st += 2 * KW;
+        if constexpr (LONG) {
+            if ((left -= 2) == 0) {
+                left = chain;
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        red[((wave * MT + mt) * 4 + j) * 64 + lane] += acc[0][mt][j];
+                        acc[0][mt][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    }
+            }
+        }
     }
 
     if (p.fetch && lane == 0 && nsteps > 0)
@@ -195,14 +221,14 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kn_kernel(DecodeParams p) {
 
     // ---- sum the waves in a fixed order (the staging LDS is reused) ----
     __syncthreads();
-    f32x4* red = reinterpret_cast<f32x4*>(smem);   // [WAVES][MT][4][64]
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
 #pragma unroll
             for (int e = 1; e < SETS; ++e) acc[0][mt][j] += acc[e][mt][j];
-            red[((wave * MT + mt) * 4 + j) * 64 + lane] = acc[0][mt][j];
+            f32x4& r = red[((wave * MT + mt) * 4 + j) * 64 + lane];
+            r = LONG ? r + acc[0][mt][j] : acc[0][mt][j];
         }
     __syncthreads();
     const bool final_out = p.split_k == 1;
