@@ -144,7 +144,7 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kn_kernel(DecodeParams p) {
     };
 
     // (a wave whose columns are all past N has none)
-    const int nsteps = n0 < p.N && st1 - st0 - kw > 0 ? (st1 - st0 - kw + KW - 1) / KW : 0;
+    const int nsteps = (NW == 1 || n0 < p.N) && st1 - st0 - kw > 0 ? (st1 - st0 - kw + KW - 1) / KW : 0;
     int st = st0 + kw;
     // two steps in flight: the loads of the next step are issued before this
     // step is staged and computed (two register sets, used alternately, so
