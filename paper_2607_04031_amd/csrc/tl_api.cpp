@@ -201,6 +201,37 @@ double w4_estimate_us(int64_t M, int64_t N, int64_t K, int tile_m, int64_t S) {
     return std::max(mfma, rounds) + 0.5 * double(N * K * 2) / 6.5e6 + partials;
 }
 
+// 256 x 256 tiles that leave the last round of workgroups part-empty (QKV at
+// M = 2048: 320 tiles on 256 CUs) cover the widest column range whose tile
+// count is a multiple of the CU count, [0, n_main); the remaining columns take
+// 128 x 128 tiles when those fit in one round (two per CU), or 256 x 256 tiles
+// of the four-wave kernel with K split 'split' ways (> 0), when those tiles
+// times the splits fill the CUs exactly and each split keeps >= 8 of the
+// 64-wide K steps (fp32 partials summed in a fixed order by a second kernel):
+// QKV at M = 2048, 64 tiles x 4 splits (on one box 1021 -> 1113 TFLOP/s against
+// the 128 x 128 tiles).
+struct Rounds {
+    int64_t n_main;
+    int split;
+};
+Rounds rounds_of_256(int64_t M, int64_t N, int64_t K) {
+    Rounds r{N, 0};
+    const int64_t mt = (M + 255) / 256, tiles = mt * (N / 256);
+    if (N % 256 || tiles <= kCUs || tiles % kCUs == 0) return r;
+    for (int64_t n1 = N - 256; n1 >= 256; n1 -= 256) {
+        if ((mt * (n1 / 256)) % kCUs) continue;
+        const int64_t rest = ((M + 127) / 128) * ((N - n1) / 128);
+        if (rest <= 2 * kCUs) r.n_main = n1;
+        break;
+    }
+    const int64_t rest256 = mt * ((N - r.n_main) / 256);
+    if (rest256 > 0 && K % 64 == 0 && kCUs % rest256 == 0) {
+        const int64_t S = kCUs / rest256;
+        if (S >= 2 && S <= 8 && K / 64 / S >= 8) r.split = int(S);
+    }
+    return r;
+}
+
 int plan_gemm(int64_t M, int64_t N, int64_t K, const tl_layout_desc* d, int32_t fetch_mode,
               Plan* P) {
     if (!d) return TL_EINVAL;
@@ -562,18 +593,19 @@ int plan_gemm(int64_t M, int64_t N, int64_t K, const tl_layout_desc* d, int32_t 
         if (!d->tile_m && !d->tile_n && M > kMediumMaxM && M % 256 != 0 && K % 64 == 0 && N % 256 == 0 &&
             !p.block_row && (!tile || 256 % p.L.br == 0) && (M < 1024 || (M + 255) / 256 * (N / 256) <= kCUs)) {
             int best_tm = 256, best_s = 1;
-            double best = 0;
             // (256-row tiles too few for a K split of 8 steps and for half the
             // CUs run as 128 x 128 tiles below, which stay)
             const int64_t t256 = (M + 255) / 256 * (N / 256);
-            if (M >= 1024 || 2 * t256 >= kCUs || K / 64 >= 16)
-                for (int64_t S = 1; S <= 8; ++S) {
-                    const double c = w4_estimate_us(M, N, K, 256, S);
-                    if (c > 0 && (best == 0 || c < best)) best = c;
-                }
-            best *= 0.9;
+            // K splits of the 256-row plan (of the column that has most), and
+            // no fewer here: fp32 chains are no longer (800 x 8192 x 4096: one
+            // split of 192-row tiles instead of two of 256-row ones took 73 us
+            // for 78 and was 4.0e-7 from the exact sums for 2.7e-7)
+            const int64_t min_s = t256 < kCUs ? std::max<int64_t>(1, std::min<int64_t>({kCUs / t256, 8, K / 64 / 8}))
+                                  : !tile || 128 % p.L.br == 0 ? std::max(1, rounds_of_256(M, N, K).split) : 1;
+            double best = 0;
+            if (M >= 1024 || 2 * t256 >= kCUs || K / 64 >= 16) best = 0.9 * w4_estimate_us(M, N, K, 256, t256 < kCUs ? min_s : 1);
             for (int c_tm : {192, 320})
-                for (int64_t S = 1; S <= 8; ++S) {
+                for (int64_t S = min_s; S <= 8; ++S) {
                     const double c = w4_estimate_us(M, N, K, c_tm, S);
                     if (c > 0 && c < best) {
                         best = c;
@@ -626,36 +658,14 @@ int plan_gemm(int64_t M, int64_t N, int64_t K, const tl_layout_desc* d, int32_t 
                 tn = 256;
             }
         }
-        // Quantisation: 256 x 256 tiles that leave the last round of
-        // workgroups part-empty (QKV at M = 2048: 320 tiles on 256 CUs) cover
-        // the widest column range whose tile count is a multiple of the CU
-        // count, and a second launch of 128 x 128 tiles covers the remaining
-        // columns when they fit in one round (two 128 x 128 workgroups per CU).
+        // whole rounds of 256 x 256 tiles and the rest, no tile requested
+        // (not with the block emulation: its count follows one tile shape)
         p.n_main = N;
         const int64_t mt = (M + tm - 1) / tm;
-        const int64_t tiles = mt * ((N + tn - 1) / tn);
-        // (not with the block emulation: its count follows one tile shape)
-        if (!d->tile_m && !d->tile_n && tm == 256 && tn == 256 && N % 256 == 0 && tiles > kCUs &&
-            tiles % kCUs != 0 && (!tile || 128 % p.L.br == 0) && !p.block_row) {
-            for (int64_t n1 = N - 256; n1 >= 256; n1 -= 256) {
-                if ((mt * (n1 / 256)) % kCUs) continue;
-                const int64_t rest = ((M + 127) / 128) * ((N - n1) / 128);
-                if (rest <= 2 * kCUs) p.n_main = n1;
-                break;
-            }
-            // The remaining columns as 256 x 256 tiles of the four-wave
-            // kernel with K split S ways, when those tiles times S fill the
-            // CUs exactly and each split keeps >= 8 of the 64-wide K steps
-            // (fp32 partials summed in a fixed order by a second kernel):
-            // QKV at M = 2048, 64 tiles x 4 splits (on one box 1021 -> 1113
-            // TFLOP/s against the 128 x 128 tiles).
-            if (p.n_main < N && K % 64 == 0) {
-                const int64_t rest256 = mt * ((N - p.n_main) / 256);
-                if (rest256 > 0 && kCUs % rest256 == 0) {
-                    const int64_t S = kCUs / rest256;
-                    if (S >= 2 && S <= 8 && K / 64 / S >= 8) p.split_rest = int(S);
-                }
-            }
+        if (!d->tile_m && !d->tile_n && tm == 256 && tn == 256 && (!tile || 128 % p.L.br == 0) && !p.block_row) {
+            const Rounds r = rounds_of_256(M, N, K);
+            p.n_main = r.n_main;
+            p.split_rest = r.split;
         }
         // Whole 256 x 256 tiles with bf16 output and an even number of
         // 64-wide K steps: a persistent grid of at most one workgroup per CU

@@ -942,8 +942,8 @@ def test_row_adaptive_edges(M, N, K, row_major):
 @pytest.mark.parametrize("M,N,K,row_major,tm,S", [
     (300, 57344, 128, False, 320, 1), (257, 57344, 192, True, 320, 1), (577, 24576, 192, False, 320, 1),
     (384, 57344, 64, True, 192, 1), (576, 57344, 64, False, 192, 1),
-    (300, 8192, 4096, False, 192, 3), (321, 8192, 4160, True, 192, 3), (300, 2560, 16384, False, 192, 8),
-    (300, 8192, 16384, False, 320, 6),
+    (300, 8192, 4096, False, 192, 4), (321, 8192, 4160, True, 192, 4), (300, 2560, 16384, False, 192, 8),
+    (300, 8192, 16384, False, 320, 6), (300, 10240, 8192, False, 192, 3), (321, 10240, 8256, True, 192, 3),
 ])
 def test_prefill_192_and_320_row_tiles(M, N, K, row_major, tm, S):
     kind = tl.TL_LAYOUT_NK_ROW if row_major else tl.TL_LAYOUT_TILE
