@@ -27,8 +27,10 @@
  *    before anything is enqueued; on an error nothing is enqueued.  A fault
  *    inside a kernel surfaces at the caller's next synchronisation.
  *  - Calls are thread-safe.  The library owns, per (device, stream), a split-K
- *    workspace and a fetch counter; concurrent calls on the SAME stream from
- *    several host threads are serialised by the stream, as usual.  A
+ *    workspace, a fetch counter and arrival counters (by which a small
+ *    weight's K splits find out that all of them are done); concurrent calls on
+ *    the SAME stream from several host threads are serialised by the stream, as
+ *    usual.  A
  *    workspace that must grow is replaced by a larger one and the old one is
  *    kept (not freed) until tl_release, so work already enqueued or captured
  *    with it stays valid.
@@ -37,9 +39,12 @@
  *    the first call on a stream, and a call that needs a larger split-K
  *    workspace than any before it on that stream, allocate device memory
  *    (hipMalloc) and must be made outside capture.  A captured graph binds
- *    the capture stream's workspace as it was at capture time: replay it on
+ *    the capture stream's workspace and arrival counters as they were at
+ *    capture time: replay it on
  *    that stream (or serialised with it), never concurrently with split-K
- *    calls on that stream, and not after tl_release.  tl_fetch_counter_read
+ *    calls on that stream, and not after tl_release.  (A replay that overlaps
+ *    such calls gives unspecified results in them, and may in the call after
+ *    them.)  tl_fetch_counter_read
  *    synchronises its stream and cannot be captured.
  */
 #ifndef TL_H_
@@ -508,7 +513,7 @@ int tl_gemm_noalloc(const void* A, const void* W, void* C, int64_t M, int64_t N,
 
 /* tl_fetch_counter_read -- synchronises 'stream', stores the weight bytes
  * tallied by tl_gemm calls made on it with TL_FETCH_COUNT since the last read
- * into *bytes, and resets the tally to zero.  Errors: TL_EINVAL for NULL
+ * into *bytes, and resets the tally (nothing else) to zero.  Errors: TL_EINVAL for NULL
  * bytes; TL_EHIP if a HIP call fails. */
 int tl_fetch_counter_read(void* stream, int64_t* bytes);
 

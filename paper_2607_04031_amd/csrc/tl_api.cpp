@@ -1,6 +1,7 @@
 // libtl C ABI: argument validation, kernel planning, per-(device, stream)
 // library state, dispatch.  Nothing is enqueued unless every check passes.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -37,9 +38,9 @@ int make_tile_layout(int64_t s, int64_t G, int64_t br, Layout* out) {
 namespace {
 
 // ---------------------------------------------------------------------------
-// Library state: split-K workspace, the fetch tally and the arrival counters
-// of K splits summed inside a launch (zero between calls), one set per
-// (device, stream).  A workspace that has to grow is retired, not freed: a
+// Library state: split-K workspace, the fetch tally and two sets of arrival
+// counters of K splits summed inside a launch (used in turn, zero between
+// calls), per (device, stream).  A workspace that has to grow is retired, not freed: a
 // HIP graph captured earlier on the stream, or a call of another thread that
 // took the old pointer, may still use it.  Retired workspaces are freed by
 // tl_release.  Each call holds a shared reference to its state, so the
@@ -50,6 +51,8 @@ struct StreamState {
     float* ws = nullptr;
     size_t ws_bytes = 0;
     unsigned long long* fetch = nullptr;   // kStateWords: the tally, then the counters
+    bool cleared = false;                  // the clear ran or is enqueued (under capture it is only recorded)
+    std::atomic<unsigned> turn{0};         // launches that used the counters
     std::vector<float*> retired;
     ~StreamState() {
         int cur = 0;
@@ -67,7 +70,15 @@ struct StateRef {
     std::shared_ptr<StreamState> keep;
     float* ws = nullptr;
     unsigned long long* fetch = nullptr;
-    unsigned* arrive = nullptr;
+
+    // the next set of counters, and the way from it to the other; nullptr
+    // where they cannot be relied on
+    unsigned* arrive(int* clear) const {
+        if (!keep || !keep->cleared) return nullptr;
+        const bool odd = keep->turn.fetch_add(1, std::memory_order_relaxed) & 1u;
+        *clear = odd ? -kArriveSet : kArriveSet;
+        return reinterpret_cast<unsigned*>(keep->fetch + kArriveAt) + (odd ? kArriveSet : 0);
+    }
 };
 
 std::mutex g_mu;
@@ -98,6 +109,8 @@ int get_state(hipStream_t stream, size_t ws_bytes, StateRef* out) {
             st.fetch = nullptr;
             return TL_EHIP;
         }
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        st.cleared = hipStreamIsCapturing(stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
     }
     if (ws_bytes > st.ws_bytes) {
         // at least double, so the retired buffers never add up to more than
@@ -112,7 +125,6 @@ int get_state(hipStream_t stream, size_t ws_bytes, StateRef* out) {
     out->keep = sp;
     out->ws = st.ws;
     out->fetch = st.fetch;
-    out->arrive = reinterpret_cast<unsigned*>(st.fetch + kArriveAt);
     return TL_OK;
 }
 
@@ -895,7 +907,7 @@ static int gemm_impl(const void* A, const void* W, const float* scales, void* C,
         if (p.pub.split_k > 1 && p.waves >= 8 && !p.block_row && !p.lds_tiles && !p.kn_wide &&
             N * K * layout->elem_bytes < (int64_t(32) << 20) && M * p.pub.tile_n * p.pub.split_k <= 4096 &&
             p.pub.workgroups / p.pub.split_k <= kArriveTiles)
-            d.arrive = st.arrive;
+            d.arrive = st.arrive(&d.arrive_clear);
         d.M = M;
         d.N = N;
         d.K = K;
@@ -1173,7 +1185,9 @@ int tl_fetch_counter_read(void* stream, int64_t* bytes) {
     unsigned long long v = 0;
     if (hipStreamSynchronize(s) != hipSuccess) return TL_EHIP;
     if (hipMemcpy(&v, st.fetch, sizeof v, hipMemcpyDeviceToHost) != hipSuccess) return TL_EHIP;
-    if (launch_zero_u64(st.fetch, s) != hipSuccess) return TL_EHIP;
+    // the tally alone: the counters behind it belong to the GEMM calls
+    const unsigned long long zero = 0;
+    if (hipMemcpyAsync(st.fetch, &zero, sizeof zero, hipMemcpyHostToDevice, s) != hipSuccess) return TL_EHIP;
     if (hipStreamSynchronize(s) != hipSuccess) return TL_EHIP;
     *bytes = int64_t(v);
     return TL_OK;

@@ -488,6 +488,7 @@ hipError_t launch_decode(const DecodeLaunch& d, hipStream_t stream) {
     p.total_rows = int(d.total_rows);
     p.scales = d.scales;
     p.arrive = d.split_k > 1 ? d.arrive : nullptr;
+    p.arrive_clear = d.arrive_clear;
     if (d.lds_tiles > 0) {   // workgroup = lds_tiles tiles x one K range
         const int grid = int(d.N / 32 / d.lds_tiles) * d.split_k;
         return launch_splitk_reduce(d, launch_lds_decode(p, d.lds_tiles, grid, stream), stream);

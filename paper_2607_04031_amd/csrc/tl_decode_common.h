@@ -43,6 +43,7 @@ struct DecodeParams {
     const float* scales;     // FP8 weights: per-output-channel scale [N], or nullptr (1)
     unsigned* arrive;        // K splits summed inside the launch (kernels with FUSE): one arrival counter per tile, else nullptr
     int swiglu_up;           // gated grouped launch: row of the first up row (I); C has N = I columns
+    int arrive_clear;        // arrive + arrive_clear: the set of counters to clear for the next such launch
 };
 
 __device__ inline uint16_t f32_to_bf16_rne(float f) {
@@ -82,13 +83,14 @@ __device__ inline bf16x8 load_stream(const uint8_t* p) {
 // K splits summed inside the launch (p.arrive): every workgroup stores its
 // fp32 partial, waits until it is out and counts itself at its tile's counter;
 // the workgroup that finds all the others' there sums the tile's partials in
-// split order -- the same sums, bit for bit, as splitk_reduce_kernel -- and
-// leaves the counter at zero for the next call.  Nobody waits for another
-// workgroup.  The splits of a tile run on different XCDs, whose L2s are not
-// coherent with each other, so partials are written through and read past
-// them (agent scope) instead of writing back a whole L2 at a fence.
-constexpr int kArriveStride = 16;        // counters are 64 bytes apart
-
+// split order -- the same sums, bit for bit, as splitk_reduce_kernel.  Nobody
+// waits for another workgroup.  The splits of a tile run on different XCDs,
+// whose L2s are not coherent with each other, so partials are written through
+// and read past them (agent scope) instead of writing back a whole L2 at a
+// fence.  A counter wraps to zero with its last arrival, in one operation, and
+// the launch clears the stream's other set of counters, which the next such
+// launch uses: a count that a launch outside the stream's order left behind
+// (a replay that overlaps other calls) is gone two such launches later.
 __device__ inline void store_partial(float* p, float v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -100,12 +102,10 @@ __device__ inline void splitk_finish(const DecodeParams& p, int tile, int n0) {
     __shared__ unsigned arrived;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // this wave's partials are out
     __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned* cnt = p.arrive + tile * kArriveStride;
-        const unsigned before = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (before == unsigned(p.split_k) - 1) __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        arrived = before;
-    }
+    if (threadIdx.x == 0) arrived = atomicInc(p.arrive + tile * kArriveStride, unsigned(p.split_k) - 1);
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < kArriveTiles; i += THREADS)
+            __hip_atomic_store(p.arrive + p.arrive_clear + i * kArriveStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     if (arrived != unsigned(p.split_k) - 1) return;     // uniform over the workgroup
     constexpr int kAhead = 8;                           // partials in flight per thread

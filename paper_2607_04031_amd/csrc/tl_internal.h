@@ -57,7 +57,10 @@ struct DecodeLaunch {
     void* C;
     float* ws;                  // [split_k][M * N rounded up to 4] partials (split_k > 1)
     unsigned long long* fetch;  // fetch tally (TL_FETCH_COUNT) or nullptr
-    unsigned* arrive = nullptr; // zeroed arrival counters, one per tile: K splits summed inside the launch
+    // K splits summed inside the launch: a zeroed set of arrival counters, and
+    // the offset of the set that it clears for the next such launch
+    unsigned* arrive = nullptr;
+    int arrive_clear = 0;
     int64_t M, N, K;
     Layout L;
     int tile_n;                 // 32 or 64
@@ -89,14 +92,18 @@ struct DecodeLaunch {
 };
 
 hipError_t launch_decode(const DecodeLaunch& d, hipStream_t stream);
-// *p = 0, enqueued on 'stream' as a one-thread kernel (not a memset node, so
-// the clear behaves like any kernel inside a captured graph)
-// a stream's device state: the fetch tally, then (kArriveAt words on) the
-// arrival counters of kArriveTiles tiles, 64 bytes apart, which are zero
-// between calls; launch_zero_u64 clears all of it
-constexpr int kArriveTiles = 2048;
+// A stream's device state, kStateWords 64-bit words: the fetch tally, then
+// (kArriveAt words on) two sets of arrival counters, one per tile, 64 bytes
+// apart.  A launch that sums its K splits itself has at least two splits and at
+// most 512 workgroups (8 or 16 waves), so at most 256 tiles.
+constexpr int kArriveTiles = 256;
+constexpr int kArriveStride = 16;              // 32-bit words between counters
+constexpr int kArriveSet = kArriveTiles * kArriveStride;
 constexpr int kArriveAt = 8;
-constexpr int kStateWords = kArriveAt + kArriveTiles * 8;
+constexpr int kStateWords = kArriveAt + kArriveSet;   // 2 sets of kArriveSet 32-bit words
+// clears the whole state at p (kStateWords words), enqueued on 'stream' as a
+// kernel (not a memset node, so the clear behaves like any kernel inside a
+// captured graph)
 hipError_t launch_zero_u64(unsigned long long* p, hipStream_t stream);
 // the fixed-order split-K reduce that follows a decode launch with split_k > 1
 // (passes 'e' through when it is an error or split_k is 1)
