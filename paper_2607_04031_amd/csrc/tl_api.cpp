@@ -781,8 +781,11 @@ MediumParams medium_params(const Plan& p, const void* A, const void* W, void* C,
 // decode kernel (which streams a group's weight once per 64 rows and reloads
 // the activations for every 64 weight rows) and no tile is requested: groups
 // of 17 - 1024 rows (1 - 300 groups) run 1.1 - 8x faster, bit for bit the same
-// results; at up to 16 rows the two are equal (within 3 %), where the decode
-// kernel stays.  Configurations, both projections at K = 4096 / 2048 (8 groups
+// results; at up to 16 rows the two are equal (within 3 %), and where few groups
+// have more (32 at most, under 10 on average) at K >= 1024 the decode kernel is
+// up to 7 % faster (gate+up of 64 groups, K = 4096, 9 rows: 164 against 172 us;
+// at 10 rows 165 and 166, and at K = 768 78 against 73): there it stays.
+// Configurations, both projections at K = 4096 / 2048 (8 groups
 // is 128 wide tiles per projection, 9 is 144), us, 192 x 256 / 128 x 128:
 //  - 192 x 256 tiles, one workgroup per CU, where there are more than half as
 //    many of them as CUs: fewest activation loads, and a group's weight is read
@@ -796,6 +799,7 @@ bool medium_grouped(const Plan& p, const tl_layout_desc* d, int64_t num_groups, 
     const int64_t kp = p.L.kind == TL_LAYOUT_TILE ? padded_cols(p.L, K) : K;
     if (256 * kp * 2 >= (int64_t(1) << 32)) return false;   // 32-bit offsets inside a tile's weight rows
     const int64_t groups = std::min(num_groups, total_rows);
+    if (max_group_rows <= 32 && total_rows < 10 * groups && K >= 1024) return false;
     const int64_t wide_cols = medium_tile_n(MediumConfig::kGroupWide) / (swiglu ? 2 : 1);
     const int64_t wide_rows = medium_tile_m(MediumConfig::kGroupWide) * groups;   // (of groups alike)
     const int64_t wide = groups * ((total_rows + wide_rows - 1) / wide_rows) * ((N + wide_cols - 1) / wide_cols);
