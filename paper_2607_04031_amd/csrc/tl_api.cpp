@@ -338,22 +338,29 @@ int plan_gemm(int64_t M, int64_t N, int64_t K, const tl_layout_desc* d, int32_t 
         p.waves = (wgs <= 2 * kCUs && p.m_tiles16 <= 2) ? 8 : 4;
         p.pub.tile_n = 64;
         // M <= 32, nothing requested: 256-column tiles with the K split that
-        // gives one round of the CUs, where that fills two thirds of it with
-        // >= 1024 K per split (45056 x 4096, 176 workgroups: 72 -> 65 us;
-        // 24576 x 4096, 192: 40 -> 37; 2048 x 8192, whose 64 workgroups do
-        // not: 12 against 29).  Past one round two workgroups share a CU, and
-        // tiles that fill 7/10 of those rounds take it (98304 x 2048, 384
-        // tiles: 77 -> 73; 81920 x 4096, 320: 122 against 130); so do 129 -
-        // 170 tiles of rows that are not whole lines, in three splits (35000 x
-        // 8192: 181 -> 146; 40000 x 4096, whole lines: 54 against 56).  At four
-        // M tiles the sums do not leave registers for it (8192 x 28672, M =
-        // 48: 119 against 220).  tile_n and workgroups report 64-column tiles
+        // gives one round of the CUs, where the columns fill three quarters of
+        // it with >= 1024 K per split (bf16 out, us, 64 / 256 columns: 45184 x
+        // 3136, 0.69 filled, M = 2 / 32: 45.6 / 45.7 and 52.7 / 59.4; 3008 x
+        // 26816, 0.72: 28.8 / 30.2 and 36.0 / 38.7; 3072 x 18304, 0.75: 26.1 /
+        // 23.6 and 32.2 / 30.3; 56576 x 1152, 0.86: 24.4 / 22.4 and 31.1 /
+        // 26.5).  Past one round two workgroups share a CU, and columns that
+        // fill 25/32 of one such round take it (99520 x 1216, 0.76: 39.1 /
+        // 43.0; 102912 x 1216, 0.79: 48.3 / 44.5; past that round 205248 x 576
+        // 39.6 / 47.8).  So do 129 - 170 tiles of rows that are not whole
+        // lines, in three splits (8 N of 33032 - 43400, K = 3072 - 8192, M = 1
+        // / 8 / 32: 1.2 - 1.4 / 1.2 - 1.4 / 1.0 - 1.25 times as fast, 43400 x
+        // 3072 at M = 32 0.98: two M tiles take it from 4096 K on); of whole
+        // lines (33024 - 43392) 64 columns unsplit are as fast.  130 shapes of
+        // one round were 0.99 - 1.4 times as fast.  At four M tiles the sums do
+        // not leave registers for it (8192 x 28672, M = 48: 119 against 220).
+        // tile_n and workgroups report 64-column tiles
         if (p.m_tiles16 <= 2 && !d->split_k && !d->tile_n && !p.block_row) {
             const int64_t wide = (N + 255) / 256, max_s = std::max<int64_t>(1, std::min<int64_t>(units / 16, kMaxSplitK));
             int64_t s1 = std::max<int64_t>(1, std::min(kCUs / wide, max_s));
-            if (N % 64 && wide > kCUs / 2 && 3 * wide <= 2 * kCUs && max_s >= 3) s1 = 3;
-            const int64_t pairs = (wide + 2 * kCUs - 1) / (2 * kCUs);   // rounds of two workgroups per CU
-            if (wide <= kCUs ? 3 * wide * s1 >= 2 * kCUs : 10 * wide >= 14 * kCUs * pairs) {
+            const bool three = N % 64 && wide > kCUs / 2 && 3 * wide <= 2 * kCUs && max_s >= 2 + p.m_tiles16;
+            if (three) s1 = 3;
+            if (three || (wide <= kCUs ? 4 * N * s1 >= 3 * 256 * kCUs
+                                       : wide <= 2 * kCUs && 32 * N >= 25 * 256 * 2 * kCUs)) {
                 S = s1;
                 p.waves = 8;
                 p.kn_wide = true;

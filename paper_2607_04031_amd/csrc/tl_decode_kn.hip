@@ -234,12 +234,11 @@ __global__ __launch_bounds__(64 * WAVES) void decode_kn_kernel(DecodeParams p) {
     const bool final_out = p.split_k == 1;
     float* part = p.ws + int64_t(split) * p.ws_stride;
     for (int e = threadIdx.x; e < NW * MT * 4 * 64; e += kThreads) {
-        const int l = e % 64, j = (e / 64) % (4 * NW), mt = e / (256 * NW);
-        const f32x4* first = red + ((j / 4 * MT + mt) * 4 + j % 4) * 64 + l;
-        f32x4 v = *first;
+        const int mt = e / (256 * NW), c = NW == 1 ? 0 : e / 256 % NW, j = e / 64 % 4, l = e % 64;
+        f32x4 v = red[((c * MT + mt) * 4 + j) * 64 + l];
 #pragma unroll
-        for (int w = 1; w < KW; ++w) v += first[w * NW * MT * 256];
-        const int n = (tile * NW * 4 + j) * 16 + (l & 15);
+        for (int w = 1; w < KW; ++w) v += red[(((w * NW + c) * MT + mt) * 4 + j) * 64 + l];
+        const int n = (NW == 1 ? n0 : (tile * NW + c) * 64) + j * 16 + (l & 15);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int m = mt * 16 + (l >> 4) * 4 + r;
