@@ -1,6 +1,8 @@
 // Weight-only 8-bit decode: FP8 (OCP E4M3) weights, bf16 activations.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "tl_decode_common.h"
 
 namespace tl {
@@ -42,6 +44,7 @@ void decode_fp8_kernel(DecodeParams p) {
     constexpr int kWaves = WAVES;
     constexpr int kThreads = 64 * WAVES;
     constexpr int TN = 16 * NS;
+    constexpr bool NARROW = MT == 1 && TILE;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int tile = blockIdx.x / p.split_k;
@@ -54,18 +57,25 @@ void decode_fp8_kernel(DecodeParams p) {
     const int n_base = tile * TN;
     const int g = lane >> 4, q = lane & 15;
     const int kg = g * 16;                     // this lane's 16 K values of a step
-    // the tile's first row as a uniform base, rows as 32-bit offsets (a tile's
-    // rows and the activations span less than 2^31 bytes, as the planner checks)
+    // row addresses: pointers, or (NARROW) 32-bit offsets from the tile's first
+    // row and from A, uniform bases (a tile's rows and the activations span
+    // less than 2^31 bytes, as the planner checks)
     auto row_off = [&](int n) -> int64_t {
         return TILE ? int64_t(n >> p.log2_br) * p.strip_bytes + (int64_t(n & ((1 << p.log2_br) - 1)) << p.log2_bc)
                     : int64_t(n) * p.K;
     };
-    const int64_t tile_off = row_off(n_base);
+    const int64_t tile_off = NARROW ? row_off(n_base) : 0;
     const uint8_t* wtile = p.W + tile_off;
+    const uint8_t* wptr[NS];
     uint32_t wrow[NS];
 #pragma unroll
-    for (int j = 0; j < NS; ++j) wrow[j] = uint32_t(row_off(min(n_base + j * 16 + q, p.N - 1)) - tile_off);
+    for (int j = 0; j < NS; ++j) {
+        const int64_t off = row_off(min(n_base + j * 16 + q, p.N - 1));
+        wptr[j] = p.W + off;
+        wrow[j] = uint32_t(off - tile_off);
+    }
     const uint8_t* Ab = reinterpret_cast<const uint8_t*>(p.A);
+    const uint16_t* aptr[MT];
     uint32_t arow[MT];
     bool aok[MT], aany[MT];
 #pragma unroll
@@ -73,8 +83,14 @@ void decode_fp8_kernel(DecodeParams p) {
         const int m = mt * 16 + q;
         aok[mt] = m < p.M;
         aany[mt] = mt * 16 < p.M;
+        aptr[mt] = p.A + int64_t(aok[mt] ? m : 0) * p.K + kg;
         arow[mt] = uint32_t((aok[mt] ? m : 0) * p.K + kg) * 2u;
     }
+    using Off = std::conditional_t<NARROW, uint32_t, int64_t>;
+    auto w_at = [&](int j, Off ko) { return reinterpret_cast<const u32x4v*>(NARROW ? wtile + (wrow[j] + uint32_t(ko)) : wptr[j] + ko); };
+    auto a_at = [&](int mt, int k) {
+        return reinterpret_cast<const bf16x8*>(NARROW ? Ab + (arow[mt] + uint32_t(k) * 2u) : reinterpret_cast<const uint8_t*>(aptr[mt] + k));
+    };
     f32x4 acc[MT][NS];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
@@ -84,19 +100,19 @@ void decode_fp8_kernel(DecodeParams p) {
     const int nsteps = st1f - st0 - wave > 0 ? (st1f - st0 - wave + kWaves - 1) / kWaves : 0;
     int st = st0 + wave;
     int i = 0;
-    auto koff = [&](int k) -> uint32_t {
-        if (TILE) return (uint32_t(k >> p.log2_bc) << p.log2_G) + uint32_t(k & p.bc_mask);
-        return uint32_t(k);
+    auto koff = [&](int k) -> Off {
+        if (TILE) return (Off(k >> p.log2_bc) << p.log2_G) + Off(k & p.bc_mask);
+        return Off(k);
     };
     auto load = [&](int k, u32x4v (&x)[NS], bf16x8 (&a)[MT][2]) {
-        const uint32_t ko = koff(k + kg);
+        const Off ko = koff(k + kg);
 #pragma unroll
-        for (int j = 0; j < NS; ++j) x[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4v*>(wtile + (wrow[j] + ko)));
+        for (int j = 0; j < NS; ++j) x[j] = __builtin_nontemporal_load(w_at(j, ko));
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             if (aany[mt]) {
-                a[mt][0] = aok[mt] ? *reinterpret_cast<const bf16x8*>(Ab + (arow[mt] + uint32_t(k) * 2u)) : zero8;
-                a[mt][1] = aok[mt] ? *reinterpret_cast<const bf16x8*>(Ab + (arow[mt] + uint32_t(k) * 2u) + 16) : zero8;
+                a[mt][0] = aok[mt] ? a_at(mt, k)[0] : zero8;
+                a[mt][1] = aok[mt] ? a_at(mt, k)[1] : zero8;
             } else {
                 a[mt][0] = zero8;
                 a[mt][1] = zero8;
@@ -139,17 +155,16 @@ void decode_fp8_kernel(DecodeParams p) {
         const bool kin = k + kg < p.K;
         u32x4v x[NS];
         bf16x8 a[MT][2];
-        const uint32_t ko = koff(kin ? k + kg : 0);
+        const Off ko = koff(kin ? k + kg : 0);
 #pragma unroll
         for (int j = 0; j < NS; ++j) {
-            const u32x4v v = __builtin_nontemporal_load(reinterpret_cast<const u32x4v*>(wtile + (wrow[j] + ko)));
+            const u32x4v v = __builtin_nontemporal_load(w_at(j, ko));
             x[j] = kin ? v : u32x4v{0u, 0u, 0u, 0u};
         }
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-            const uint8_t* pa = Ab + (kin ? arow[mt] + uint32_t(k) * 2u : arow[mt] - uint32_t(kg) * 2u);
-            const bf16x8 v0 = *reinterpret_cast<const bf16x8*>(pa);
-            const bf16x8 v1 = *reinterpret_cast<const bf16x8*>(pa + 16);
+            const bf16x8* pa = a_at(mt, kin ? k : -kg);
+            const bf16x8 v0 = pa[0], v1 = pa[1];
             a[mt][0] = kin && aok[mt] ? v0 : zero8;
             a[mt][1] = kin && aok[mt] ? v1 : zero8;
         }
