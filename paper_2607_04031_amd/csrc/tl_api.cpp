@@ -88,6 +88,11 @@ int current_device(int* dev) {
     return hipGetDevice(dev) == hipSuccess ? TL_OK : TL_EHIP;
 }
 
+bool capturing(hipStream_t stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(stream, &status) != hipSuccess || status != hipStreamCaptureStatusNone;
+}
+
 // Looks up (current device, stream), creating its tally and counters (cleared
 // on 'stream', so the clear is ordered before any kernel that uses it) and growing its
 // workspace to at least ws_bytes.  The lock covers the map and the
@@ -109,8 +114,7 @@ int get_state(hipStream_t stream, size_t ws_bytes, StateRef* out) {
             st.fetch = nullptr;
             return TL_EHIP;
         }
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        st.cleared = hipStreamIsCapturing(stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
+        st.cleared = !capturing(stream);
     }
     if (ws_bytes > st.ws_bytes) {
         // at least double, so the retired buffers never add up to more than
@@ -911,13 +915,18 @@ static int gemm_impl(const void* A, const void* W, const float* scales, void* C,
         // partials quickly (4096 floats; one MI355X, eager / in a graph, us:
         // 1 x 1024 x 1024 10.9 -> 7.8 / 5.7 -> 5.4, 16 x 1024 x 4096, S = 8:
         // 10.1 -> 7.5 / 7.7 -> 7.1; past the line 64 x 512 x 7168, S = 14:
-        // 10.3 against 12.5 / 10.0 against 12.5).  On large weights every
-        // workgroup would hold its CU while its partials are written out
-        // (Llama-70B layer at M = 8: 260 against 267 us).  More than 512
-        // workgroups (4 waves) and the block emulation keep the second launch.
+        // 10.3 against 12.5 / 10.0 against 12.5) and all workgroups run at
+        // once: each holds its CU while its partials are written out (43 x
+        // 4608 x 1024 row-major, 288 workgroups: 12.6 against 13.9 eager, 36 x
+        // 4864 x 1024, 304: 12.1 against 13.1; Llama-70B layer at M = 8: 260
+        // against 267).  More than 512 workgroups (4 waves) and the block
+        // emulation keep the second launch.  In a graph the host's part is
+        // gone; there two launches are faster for FP8 (30 shapes of 1 - 61
+        // rows: 0.82 - 1.03 x summed inside; bf16 0.97 - 1.19) and for columns
+        // summed one by one (N % 4) of more than 32 rows (0.92 - 1.01)
         if (p.pub.split_k > 1 && p.waves >= 8 && !p.block_row && !p.lds_tiles && !p.kn_wide &&
             N * K * layout->elem_bytes < (int64_t(32) << 20) && M * p.pub.tile_n * p.pub.split_k <= 4096 &&
-            p.pub.workgroups / p.pub.split_k <= kArriveTiles)
+            p.pub.workgroups <= kCUs && ((!p.fp8 && (N % 4 == 0 || M <= 32)) || !capturing(s)))
             d.arrive = st.arrive(&d.arrive_clear);
         d.M = M;
         d.N = N;

@@ -95,8 +95,8 @@ hipError_t launch_decode(const DecodeLaunch& d, hipStream_t stream);
 // A stream's device state, kStateWords 64-bit words: the fetch tally, then
 // (kArriveAt words on) two sets of arrival counters, one per tile, 64 bytes
 // apart.  A launch that sums its K splits itself has at least two splits and at
-// most 512 workgroups (8 or 16 waves), so at most 256 tiles.
-constexpr int kArriveTiles = 256;
+// most one workgroup per CU, so at most 128 tiles.
+constexpr int kArriveTiles = 128;
 constexpr int kArriveStride = 16;              // 32-bit words between counters
 constexpr int kArriveSet = kArriveTiles * kArriveStride;
 constexpr int kArriveAt = 8;

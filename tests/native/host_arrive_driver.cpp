@@ -97,9 +97,20 @@ int main() {
     CHECK(!call(TL_LAYOUT_TILE, 2, 1, 1024, 1024, 1, 1));       // not split
     CHECK(!call(TL_LAYOUT_TILE, 2, 1, 4096, 4096, 4, 1));       // 32 MB
     CHECK(!call(TL_LAYOUT_TILE, 2, 8, 10240, 8192, 0, 1));
-    CHECK(call(TL_LAYOUT_TILE, 2, 1, 8192, 1024, 2, 1));        // 512 workgroups of 8 waves, 256 tiles
-    CHECK(!call(TL_LAYOUT_TILE, 2, 1, 8192, 1024, 3, 1));       // 768, of 4
+    CHECK(call(TL_LAYOUT_TILE, 2, 1, 4096, 1024, 2, 1));        // 256 workgroups, 128 tiles
+    CHECK(!call(TL_LAYOUT_TILE, 2, 1, 4128, 1024, 2, 1));       // 258
+    CHECK(!call(TL_LAYOUT_TILE, 2, 1, 8192, 1024, 3, 1));       // 768, of 4 waves
     CHECK(!call(TL_LAYOUT_TILE, 2, 1, 1024, 1024, 0, 1, true)); // allocation-free: two launches
+
+    // under capture those that are faster so on the GPU alone
+    g_capturing = true;
+    CHECK(call(TL_LAYOUT_TILE, 2, 1, 1024, 1024, 0, 1));
+    CHECK(!call(TL_LAYOUT_TILE, 1, 1, 1024, 2048, 0, 1));
+    CHECK(!call(TL_LAYOUT_TILE, 2, 33, 1002, 1024, 2, 1));
+    CHECK(call(TL_LAYOUT_TILE, 2, 33, 1004, 1024, 2, 1));
+    CHECK(call(TL_LAYOUT_TILE, 2, 32, 1002, 1024, 2, 1));
+    g_capturing = false;
+    CHECK(call(TL_LAYOUT_TILE, 2, 33, 1002, 1024, 2, 1));
 
     // the two sets of counters are used in turn, on each stream its own, also
     // when other calls come between

@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 CALLS = [
     (tl.TL_LAYOUT_TILE, 2, 1, 1024, 1024, 0), (tl.TL_LAYOUT_NK_ROW, 2, 16, 1024, 4096, 8), (tl.TL_LAYOUT_KN_ROW, 2, 8, 2048, 2048, 4),
     (tl.TL_LAYOUT_TILE, 1, 4, 1024, 2048, 0), (tl.TL_LAYOUT_NK_ROW, 1, 5, 1001, 2048, 4), (tl.TL_LAYOUT_KN_ROW, 2, 17, 264, 4096, 3),
-    (tl.TL_LAYOUT_NK_ROW, 2, 3, 998, 2048, 5), (tl.TL_LAYOUT_TILE, 1, 17, 256, 8192, 6), (tl.TL_LAYOUT_TILE, 2, 2, 8192, 1024, 2),
+    (tl.TL_LAYOUT_NK_ROW, 2, 3, 998, 2048, 5), (tl.TL_LAYOUT_TILE, 1, 17, 256, 8192, 6), (tl.TL_LAYOUT_TILE, 2, 2, 4096, 1024, 2),
     (tl.TL_LAYOUT_KN_ROW, 2, 1, 64, 16384, 16), (tl.TL_LAYOUT_TILE, 2, 33, 96, 1024, 2),
 ]
 
