@@ -46,7 +46,9 @@
 // once takes 183 us.  Groups of 200 rows, two chunks: 1493 -> 383 us.
 // Non-temporal weight loads, taken when a group's rows
 // fit one tile, are part of that (512 tokens: 228 -> 213 us); with row chunks
-// that share the weight they cost (8 groups of 256 rows: 158 -> 165 us), as
+// that share the weight they cost (8 groups of 256 rows: 158 -> 165 us), and
+// with rows of W that are not whole lines, whose ends two K steps share (96 x
+// 57701 x 1992 row-major: 71.9 -> 78.2 us with them, 70.3 without), as
 // does starting each workgroup at another K step (no gain, the tile's strips
 // do not collide in HBM).
 #include <hip/hip_runtime.h>
@@ -138,7 +140,10 @@ __global__ __launch_bounds__(128 * WN) __attribute__((amdgpu_waves_per_eu(2, 2))
 
     // ---- which rows and columns ----
     int nt, split = 0, row0, rows;               // output rows [row0, row0 + rows)
-    bool w_once = true;                          // no other workgroup reads this tile's weight
+    // non-temporal weight loads: no other workgroup reads the tile's weight, and
+    // a K step ends where a line of it does
+    const bool lines = TILE || p.K % 64 == 0;
+    bool w_once = lines;
     const uint8_t* W = p.W;
     if constexpr (GROUPED) {
         // units in use: group by group, in a group tile by tile, in a tile
@@ -201,7 +206,7 @@ __global__ __launch_bounds__(128 * WN) __attribute__((amdgpu_waves_per_eu(2, 2))
         const int b0 = int(int64_t(blocks) * chunk / int(chunks)), b1 = int(int64_t(blocks) * (chunk + 1) / int(chunks));
         row0 = r0 + b0 * 32;
         rows = min(r0 + b1 * 32, r1) - row0;
-        w_once = chunks == 1;
+        w_once = lines && chunks == 1;
         W += int64_t(group) * p.group_stride;
     } else {
         // one weight, all rows in one tile: column tiles, then K splits; each
