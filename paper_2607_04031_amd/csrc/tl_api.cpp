@@ -657,7 +657,12 @@ int plan_gemm(int64_t M, int64_t N, int64_t K, const tl_layout_desc* d, int32_t 
             if (t256 < kCUs) {
                 const int64_t S = std::min<int64_t>({kCUs / t256, 8, K / 64 / 8});
                 if (S >= 2) {
-                    if (M <= kMediumMaxM) {
+                    // (seven row blocks on at most half of the CUs over long K
+                    // ranges are MFMA work on an idle chip, which the four-wave
+                    // kernel does with fewer LDS reads: M = 200, 3072 x 28672
+                    // 78 us against 85, 768 x 25600 68 against 71; 2400 K per
+                    // split, 160 workgroups or M = 192: even or slower)
+                    if (M <= kMediumMaxM && !(M > 192 && 2 * t256 * S <= kCUs && K >= 2560 * S)) {
                         p.medium = true;
                         p.medium_cfg = MediumConfig::kWide;
                     } else {
