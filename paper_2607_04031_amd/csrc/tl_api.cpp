@@ -728,8 +728,13 @@ int plan_gemm(int64_t M, int64_t N, int64_t K, const tl_layout_desc* d, int32_t 
         // 231 / 243 -> 176 / 205 / 227 / 248, QKV (S = 6) 56.9 / 60.0 / 63.3 /
         // 63.5 -> 44.8 / 51.7 / 56.9 / 61.5: even at 256 rows, where a full
         // tile is MFMA work that the four-wave kernel does with fewer LDS reads.
+        // Not above 80 rows of C that do not all start on 16 bytes, over a K so
+        // short that storing them piecemeal is what counts (M = 128, 38201 x
+        // 1024 27 us against 30, 46375 x 768 25.9 against 27.6; x 2048 even,
+        // M = 65 1.05 x as fast).
+        const bool short_odd = M > 80 && K <= 1280 && N % (p.out_bf16 ? 8 : 4) != 0;
         if (!d->tile_m && !d->tile_n && M <= kMediumMaxM && !p.block_row && !p.split_rest &&
-            mt == 1 && p.n_main == N) {
+            mt == 1 && p.n_main == N && !short_odd) {
             p.medium = true;
             p.medium_cfg = tn == 256 ? MediumConfig::kWide : MediumConfig::kNarrow;
             p.persist = false;
