@@ -218,12 +218,12 @@ int tl_unpack(const void* src_tm, void* dst, int64_t rows, int64_t cols, int32_t
  * M <= 64 runs the decode kernel (skinny GEMM, HBM-bound; at 17 <= M <= 32
  * on tile-major weights whose 32-row tiles and 512-column K chunks fill the
  * CUs in whole rounds, and at 33 <= M <= 64 where groups of four such tiles
- * and the K ranges fill at least 7/8 of one round, a variant that stages the
- * activations in LDS and shares them across several tiles) -- except that
- * at 33 <= M <= 64 a bf16
+ * and the K ranges fill at least 7/8 of one round, a variant that stages
+ * weights and activations in LDS and shares the activations across several
+ * tiles) -- except that at 33 <= M <= 64 a bf16
  * weight read natively with N >= 32768 (its 128x128 tiles fill the CUs), no
- * tile or split requested and the prefill kernel's limits met, takes the
- * prefill kernel's 128x128 tiles; larger M runs the prefill kernels (bf16
+ * tile or split requested and the prefill kernels' limits met, takes
+ * the row-adaptive kernel's 128x128 tiles; larger M runs the prefill kernels (bf16
  * MFMA tiles 256x256x64, 256x320x64, 192x256x64, 320x256x64, 256x128x64 or
  * 128x128x64, MFMA-bound;
  * with bf16 output, whole 256x256 tiles and K % 128 == 0 a persistent grid of
@@ -234,9 +234,11 @@ int tl_unpack(const void* src_tm, void* dst, int64_t rows, int64_t cols, int32_t
  * workgroups, or 128x128 tiles; when 256x256 tiles are fewer than the CUs
  * (and K % 64 == 0, N % 256 == 0), every column takes them with K split, up
  * to 8 ways -- at M <= 128, 128x128 tiles with K split when those are fewer
- * than the CUs (N % 128 == 0); with M <= 224 in one row of tiles they run on
- * the row-adaptive kernel; above, 192- or 320-row tiles where they leave
- * fewer padded rows; see tl_gemm_plan).  layout->elem_bytes = 1 means an FP8 weight (OCP E4M3, one
+ * than the CUs (N % 128 == 0).  With M <= 224 in one row of tiles they run on
+ * the row-adaptive kernel, which computes only the 32-row blocks that exist;
+ * above, 192- or 320-row tiles, with at least as many K splits, take the place
+ * of 256-row ones where they leave fewer padded rows; see tl_gemm_plan).
+ * layout->elem_bytes = 1 means an FP8 weight (OCP E4M3, one
  * byte per element, e.g. 64 x 64 memory tiles of 4 KB, Section 3.1): decode
  * kernel only, converted exactly to bf16 in registers (see tl_gemm_w8 for
  * per-channel scales).

@@ -180,10 +180,10 @@ struct Plan {
     int64_t fetch_G = 0;
     int64_t n_main = 0;          // prefill: columns covered by the main tiles (rest: 128 x 128)
     bool fp8 = false;            // 1-byte (OCP E4M3) weight, decode kernel
-    int lds_tiles = 0;           // > 0: decode with activations staged in LDS, tiles per workgroup
-    bool kn_wide = false;        // that kernel with 256 columns per workgroup
+    int lds_tiles = 0;           // > 0: decode with weights and activations staged in LDS, tiles per workgroup
     bool kn_row = false;         // weight stored [K][N] (N contiguous): the transposing decode kernel
-    int split_rest = 0;          // prefill: K splits of the 256 x 256 tiles past n_main (0: 128 x 128 tiles)
+    bool kn_wide = false;        // that kernel with 256 columns per workgroup
+    int split_rest = 0;          // prefill: K splits of the tile_m x 256 tiles past n_main (0: 128 x 128 tiles)
     bool persist = false;        // prefill: one workgroup per CU walks the main launch's tiles
     bool medium = false;         // all rows in one tile of the row-adaptive kernel
     MediumConfig medium_cfg = MediumConfig::kNarrow;
@@ -311,11 +311,11 @@ int plan_gemm(int64_t M, int64_t N, int64_t K, const tl_layout_desc* d, int32_t 
     if (p.fp8 && !(M <= kDecodeMaxM && d->tile_m <= 64)) return TL_EUNSUPPORTED;        // FP8: decode kernel only
     // 33 <= M <= 64 on a wide bf16 weight (128 x 128 tiles fill the CUs at
     // least once: N >= 32768), no tile or split requested, within the
-    // prefill kernel's limits (whole memory-tile strips per 128-row tile,
+    // row-adaptive kernel's limits (whole memory-tile strips per 128-row tile,
     // weights under 4 GB): its 128 x 128 tiles stream the weight faster than
     // the decode kernel's 64-row tiles at four 16-row M tiles, whose
     // activation reloads from L2 match the weight bytes (Llama gate+up, bf16
-    // out, one box, M = 33 / 48 / 64: 187 / 211 / 240 -> 169 / 171 / 172 us)
+    // out, one box, M = 33 / 48 / 64: 185 / 211 / 240 -> 139 / 141 / 145 us)
     const bool wide_mid_m = M > 32 && M <= kDecodeMaxM && !d->tile_m && !d->tile_n && !d->split_k && !p.fp8 &&
                             !p.kn_row && !p.block_row && N / 128 >= kCUs && (!tile || 128 % p.L.br == 0) &&
                             (tile ? packed_bytes(p.L, N, K) : N * K * 2) < (int64_t(1) << 32);
@@ -748,10 +748,11 @@ int plan_gemm(int64_t M, int64_t N, int64_t K, const tl_layout_desc* d, int32_t 
     return TL_OK;
 }
 
-// A grouped launch runs the decode kernel over every group's weight with
+// A grouped launch on the decode kernel: every group's weight with
 // 4-wave workgroups, one per (group, tile) and no K split; the group row
 // bound only chooses the 16-row M tiles per pass (larger groups take more
-// passes over their weights).
+// passes over their weights).  medium_grouped below says which launches take
+// the row-adaptive kernel instead; what this plan refuses, those refuse too.
 int plan_grouped(int64_t max_group_rows, int64_t N, int64_t K, const tl_layout_desc* d, int32_t fetch_mode,
                  Plan* P) {
     if (!d || max_group_rows < 1) return TL_EINVAL;

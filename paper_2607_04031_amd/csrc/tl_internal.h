@@ -52,25 +52,25 @@ hipError_t launch_repack(const void* src, void* dst, int64_t rows, int64_t cols,
 struct MediumLaunch;
 
 struct DecodeLaunch {
-    const uint16_t* A;
-    const uint8_t* W;
-    void* C;
-    float* ws;                  // [split_k][M * N rounded up to 4] partials (split_k > 1)
-    unsigned long long* fetch;  // fetch tally (TL_FETCH_COUNT) or nullptr
+    const uint16_t* A = nullptr;
+    const uint8_t* W = nullptr;
+    void* C = nullptr;
+    float* ws = nullptr;        // [split_k][M * N rounded up to 4] partials (split_k > 1)
+    unsigned long long* fetch = nullptr;  // fetch tally (TL_FETCH_COUNT) or nullptr
     // K splits summed inside the launch: a zeroed set of arrival counters, and
     // the offset of the set that it clears for the next such launch
     unsigned* arrive = nullptr;
     int arrive_clear = 0;
-    int64_t M, N, K;
-    Layout L;
-    int tile_n;                 // 32 or 64
-    int m_tiles16;              // ceil(M / 16): 1, 2 or 4
-    int waves;                  // wavefronts per workgroup: 4, 8 or 16 (K split inside)
-    int split_k;
-    int64_t k_unit;             // K granularity of a split, in elements
-    bool out_bf16;
-    bool block_fetch;           // row-major weight read in whole fetch_G-byte blocks
-    int64_t fetch_G;
+    int64_t M = 0, N = 0, K = 0;
+    Layout L = {};
+    int tile_n = 0;             // 32 or 64
+    int m_tiles16 = 0;          // ceil(M / 16): 1, 2 or 4
+    int waves = 0;              // wavefronts per workgroup: 4, 8 or 16 (K split inside)
+    int split_k = 1;
+    int64_t k_unit = 0;         // K granularity of a split, in elements
+    bool out_bf16 = false;
+    bool block_fetch = false;   // row-major weight read in whole fetch_G-byte blocks
+    int64_t fetch_G = 0;
     // grouped launch (num_groups > 0; split_k 1, waves 4): group e has weight
     // W + e * group_stride and output rows [group_offsets[e], group_offsets[e+1])
     int num_groups = 0;
@@ -85,9 +85,12 @@ struct DecodeLaunch {
     // FP8 (E4M3) weight, bf16 activations; optional per-output-channel scales [N]
     bool fp8 = false;
     const float* scales = nullptr;
-    const MediumLaunch* medium = nullptr;   // a launch of the row-adaptive kernel (the K-split fields apply to its reduce)
+    // a launch of the row-adaptive kernel: of the fields above, those of the
+    // split-K reduce apply (C, ws, M, N, split_k, out_bf16)
+    const MediumLaunch* medium = nullptr;
     bool kn_wide = false;       // [K][N] weight: 256-column tiles (M <= 32)
-    // > 0: the LDS kernel with this many 32-row tiles per workgroup (17 <= M <= 64, tile-major, N % (32 lds_tiles) == 0, K % 512 == 0)
+    // > 0: the LDS kernel with this many 32-row tiles per workgroup (17 <= M <= 64,
+    // tile-major, N % (32 lds_tiles) == 0, K % 512 == 0, their rows below 4 GB)
     int lds_tiles = 0;
 };
 
@@ -121,15 +124,15 @@ struct PrefillLaunch {
     unsigned long long* fetch;
     int64_t M, N, K;
     Layout L;
-    int tile_m;                 // 128 or 256
-    int tile_n;                 // 128, 256 or 320 (256 and 320 only with tile_m 256; 320 persistent)
+    int tile_m;                 // 128 or 256; 192 or 320 with tile_n 256 (not persistent)
+    int tile_n;                 // 128, 256 or 320 (256 not with tile_m 128; 320 only with 256, persistent)
     bool out_bf16;
     // columns [0, n_main) use tile_m x tile_n tiles; columns [n_main, N), if
     // any, a second launch of 128 x 128 tiles (n_main is a multiple of tile_n)
     int64_t n_main;
     bool block_fetch = false;   // row-major weight read in whole fetch_G-byte blocks
     int64_t fetch_G = 0;
-    // > 1: columns [n_main, N) run as 256 x 256 tiles with K split this many
+    // > 1: columns [n_main, N) run as tile_m x 256 tiles with K split this many
     // ways (fp32 partials in ws, M * (N - n_main) floats per split) instead
     // of 128 x 128 tiles
     int split_rest = 0;
