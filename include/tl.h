@@ -299,10 +299,9 @@ int tl_gemm_plan(int64_t M, int64_t N, int64_t K, const tl_layout_desc* layout,
  *                Out-of-order offsets give unspecified rows of C, never an
  *                access outside A, W or C.
  * max_group_rows: host bound on the rows of one group; it picks the kernel and
- *                its M tile: the decode kernel with 16 rows up to 16 (up to 32
- *                where groups have few on average, or a tile is requested: 32
- *                or 64), above that the row-adaptive
- *                kernel with up to 192 rows.  A group with more rows is
+ *                its M tile: the decode kernel with 16, 32 or 64 rows for few
+ *                rows, or little weight, or where a tile is requested, else the
+ *                row-adaptive kernel with up to 192.  A group with more rows is
  *                processed in several passes over its weight (correct, more
  *                traffic).  Results do not depend on it.
  * W:             device, group_stride bytes apart (a multiple of 16, at least

@@ -799,16 +799,28 @@ MediumParams medium_params(const Plan& p, const void* A, const void* W, void* C,
 }
 
 // Whether a grouped launch takes the row-adaptive kernel, its configuration
-// and its grid.  It does when a group may exceed one 16-row MFMA tile of the
-// decode kernel (which streams a group's weight once per 64 rows and reloads
-// the activations for every 64 weight rows) and no tile is requested: groups
-// of 17 - 1024 rows (1 - 300 groups) run 1.1 - 8x faster, bit for bit the same
-// results; at up to 16 rows the two are equal (within 3 %), and where few groups
-// have more (32 at most, under 10 on average) at K >= 1024 the decode kernel is
-// up to 7 % faster (gate+up of 64 groups, K = 4096, 9 rows: 164 against 172 us;
-// at 10 rows 165 and 166, and at K = 768 78 against 73): there it stays.
-// Configurations, both projections at K = 4096 / 2048 (8 groups
-// is 128 wide tiles per projection, 9 is 144), us, 192 x 256 / 128 x 128:
+// and its grid; the results are the same bits on either.  The decode kernel
+// streams a group's weight once per 64 rows and reloads the activations for
+// every 32 or 64 weight rows; its many small workgroups, whose four waves split
+// K, have the shorter chain of loads where the chip is not full.  So it stays,
+// by the rows that the largest group is likely to have (the bound, or twice the
+// average where the bound is loose; both sides measured over 650 shapes of 1 -
+// 300 groups of 6 - 512 rows, K = 256 - 5000, most of them cold; on average the
+// rule is within 1 % of the faster side),
+//  - up to 32 rows, unless the weights are hundreds of MB in whole 256-row tiles
+//    and the groups have 10 rows or more on average (gate+up of 138 groups of 23
+//    rows, 768 x 800: 1.1 x as fast here; else 0.5 - 1.2 x, mostly below 1: 3
+//    groups of 24 rows, 2496 x 4064, 18.9 us there, 35.7 here);
+//  - up to 64, on at most 256 tiles of 64 weight rows (0.73 - 1.07 x: 168 tiles,
+//    2688 x 2240, 18.8 against 24.1; past them 1.2 - 2.4 x), or 600 of groups
+//    that have under 13 on average and 32-row tiles (0.90 - 1.0 x);
+//  - up to 128 (two passes), on at most 120, where its tiles have 32 rows (0.73 -
+//    1.0 x: 4 groups of 67, 1088 x 2304, 27.9 against 31.7; with 64 rows 1.1 -
+//    1.5 x);
+//  - where a tile is requested.
+// Elsewhere this one is 1.0 - 4 x as fast.  Configurations, both projections at
+// K = 4096 / 2048 (8 groups is 128 wide tiles per projection, 9 is 144), us, 192
+// x 256 / 128 x 128:
 //  - 192 x 256 tiles, one workgroup per CU, where there are more than half as
 //    many of them as CUs: fewest activation loads, and a group's weight is read
 //    by one workgroup up to 192 rows (9 groups of 30 / 100 / 150 rows: 84 /
@@ -821,7 +833,14 @@ bool medium_grouped(const Plan& p, const tl_layout_desc* d, int64_t num_groups, 
     const int64_t kp = p.L.kind == TL_LAYOUT_TILE ? padded_cols(p.L, K) : K;
     if (256 * kp * 2 >= (int64_t(1) << 32)) return false;   // 32-bit offsets inside a tile's weight rows
     const int64_t groups = std::min(num_groups, total_rows);
-    if (max_group_rows <= 32 && total_rows < 10 * groups && K >= 1024) return false;
+    const int64_t w_rows = swiglu ? 2 * N : N, tiles64 = groups * ((w_rows + 63) / 64);
+    const int64_t bound = std::min(max_group_rows, total_rows);
+    const int64_t likely = std::min(bound, std::max<int64_t>(33, 2 * total_rows / groups));
+    const bool tile32 = p.pub.tile_n == 32;
+    if (likely <= 32 && !(w_rows % 256 == 0 && total_rows >= 10 * groups && groups * w_rows * K * 2 >= 384000000))
+        return false;
+    if (likely <= 64 && tiles64 <= (tile32 && total_rows < 13 * groups ? 600 : 256)) return false;
+    if (likely <= 128 && tile32 && tiles64 <= 120) return false;
     const int64_t wide_cols = medium_tile_n(MediumConfig::kGroupWide) / (swiglu ? 2 : 1);
     const int64_t wide_rows = medium_tile_m(MediumConfig::kGroupWide) * groups;   // (of groups alike)
     const int64_t wide = groups * ((total_rows + wide_rows - 1) / wide_rows) * ((N + wide_cols - 1) / wide_cols);

@@ -316,7 +316,7 @@ def test_swiglu_graph_replay():
     parity(host_f32(eager), oracle.grouped_swiglu_f64(A, ids, offsets, Ws), "swiglu graph")
 
 
-# Groups past 16 rows take the row-adaptive kernel: row counts at the edges of
+# Groups past 16 rows may take the row-adaptive kernel: row counts at the edges of
 # its 32-row blocks and of its 128-, 192- and 256-row tiles, K below, at and
 # past its 64-wide steps, N around its 128 and 256 columns.  The bound on the
 # largest group (max_rows) and the number of groups select the configuration.

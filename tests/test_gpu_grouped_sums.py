@@ -1,6 +1,6 @@
-"""Grouped GEMMs past 16 rows (the row-adaptive kernel) add the same products in
-the same order as the decode kernel, which a requested tile selects: the results
-are equal bit for bit, in fp32 too, whatever the number of rows of a group, the
+"""The row-adaptive kernel's grouped GEMMs add the same products in the same order
+as the decode kernel's, which a requested tile selects: the results are equal bit
+for bit, in fp32 too, whatever the number of rows of a group, the bound on it, the
 configuration and the layout."""
 import numpy as np
 import pytest
@@ -20,9 +20,12 @@ def dev_i32(a):
 # groups around the 32-row blocks and the 128- and 192-row tiles, more than one
 # chunk, empty ones; K below one step, of one to five (fewer than, as many as and
 # more than the four sums), with a part of a step, and long; few tiles (128 x 128)
-# and many (192 x 256); more than 64 and more than 256 groups
+# and many (192 x 256); more than 64 and more than 256 groups.  With a bound of 129
+# rows or more all of them take the row-adaptive kernel: groups with more than 64
+# rows on average, or more than 600 tiles of 64 weight rows, or 64-row tiles and
+# more than 32 rows
 CASES = [
-    ([17, 0, 1, 32], 96, 24), ([33, 64, 0, 65], 320, 64), ([128, 129, 3], 160, 136), ([192, 0, 193, 31], 128, 192),
+    ([17, 0, 1, 32] * 80, 96, 24), ([33, 64, 0, 65], 320, 64), ([128, 129, 3], 160, 136), ([192, 0, 193, 31], 128, 192),
     ([256, 255, 5], 288, 200), ([257, 16, 400], 64, 256), ([190, 40, 385], 128, 328), ([100, 250], 256, 8192),
     ([20] * 70, 800, 128), ([90, 0, 20, 193] * 33, 512, 968), ([17, 0, 3, 40] * 80, 256, 320),
 ]
@@ -53,10 +56,11 @@ def test_same_bits_as_the_decode_kernel(counts, N, K, swiglu, kind):
     fn = tl.tl_gemm_grouped_swiglu if swiglu else tl.tl_gemm_grouped
     fetch = tl.TL_FETCH_BLOCK if tile else tl.TL_FETCH_NATIVE
     got = []
-    for tile_m in (0, 64):
+    for tile_m, bound in ((64, max(counts)), (0, max(counts)), (0, max(129, max(counts)))):
         C = torch.full((T, N), float("nan"), dtype=torch.float32, device="cuda")
         d = tl.layout(kind=kind, G=1024, block_rows=16, tile_m=tile_m, out_dtype=tl.TL_OUT_F32)
-        fn(A, a_rows, ids, offsets, E, T, max(counts), stack, stride, C, N, K, d, fetch)
+        fn(A, a_rows, ids, offsets, E, T, bound, stack, stride, C, N, K, d, fetch)
         got.append(C)
     assert torch.equal(got[0], got[1])
+    assert torch.equal(got[0], got[2])
 
