@@ -195,6 +195,7 @@ constexpr int64_t kMaxDim = int64_t(1) << 30;   // largest M, N or K
 constexpr int kTargetWorkgroups = 1024;   // 4 per CU on 256 CUs
 constexpr int kMaxSplitK = 16;            // partials the reduce kernel sums
 constexpr int kCUs = 256;                  // MI355X compute units
+constexpr int64_t kLastLevelBytes = int64_t(256) << 20;   // its last level of cache
 
 // Estimated time (us) of prefill_w4_kernel with tile_m x 256 tiles and K split
 // S ways, 0 where that is no plan: the larger of the padded rows' MFMA work at
@@ -728,13 +729,17 @@ int plan_gemm(int64_t M, int64_t N, int64_t K, const tl_layout_desc* d, int32_t 
         // 231 / 243 -> 176 / 205 / 227 / 248, QKV (S = 6) 56.9 / 60.0 / 63.3 /
         // 63.5 -> 44.8 / 51.7 / 56.9 / 61.5: even at 256 rows, where a full
         // tile is MFMA work that the four-wave kernel does with fewer LDS reads.
-        // Not above 80 rows of C that do not all start on 16 bytes, over a K so
-        // short that storing them piecemeal is what counts (M = 128, 38201 x
-        // 1024 27 us against 30, 46375 x 768 25.9 against 27.6; x 2048 even,
-        // M = 65 1.05 x as fast).
-        const bool short_odd = M > 80 && K <= 1280 && N % (p.out_bf16 ? 8 : 4) != 0;
+        // Not with rows of C that do not all start on 16 bytes (the columns are
+        // stored one by one), where that counts: above 80 rows over a short K
+        // (M = 128, 38201 x 1024 27 us against 30, 46375 x 768 25.9 against
+        // 27.6; M = 65 1.05 x as fast), above 88 in more than one round of a
+        // weight that the last level of cache can hold (12 shapes of 97 - 112 /
+        // 113 - 128 rows 1.00 / 0.97 x as fast from HBM, 0.96 / 0.91 x from the
+        // cache; 96 rows 1.01 and 0.95 - 0.98 x, fewer 1.01 x or more).
+        const bool odd = N % (p.out_bf16 ? 8 : 4) != 0 &&
+                         ((M > 80 && K <= 1280) || (M > 88 && p.pub.workgroups > kCUs && N * K * 2 < kLastLevelBytes));
         if (!d->tile_m && !d->tile_n && M <= kMediumMaxM && !p.block_row && !p.split_rest &&
-            mt == 1 && p.n_main == N && !short_odd) {
+            mt == 1 && p.n_main == N && !odd) {
             p.medium = true;
             p.medium_cfg = tn == 256 ? MediumConfig::kWide : MediumConfig::kNarrow;
             p.persist = false;
@@ -795,6 +800,7 @@ MediumParams medium_params(const Plan& p, const void* A, const void* W, void* C,
     m.bc_mask = tile ? int(p.L.bc - 1) : 0;
     m.out_bf16 = p.out_bf16;
     m.n_tiles = int((N + cols - 1) / cols);
+    m.w_stream = tile || K % 64 == 0;
     return m;
 }
 
@@ -922,6 +928,14 @@ static int gemm_impl(const void* A, const void* W, const float* scales, void* C,
         m.split_k = p.pub.split_k;
         m.ws = st.ws;
         m.ws_stride = (M * N + 3) / 4 * 4;
+        // Non-temporal loads keep a weight out of the last level of cache.  One
+        // that fits would be read from there by a next call: in more than one
+        // round of workgroups plain loads then are 8 - 20 % faster (M = 128,
+        // 44544 x 2312: 62.4 -> 47.6 us, 128 x 128 tiles of tl_prefill.hip 46.9)
+        // and 4 - 7 % slower from HBM (61.2 -> 64.3; 67.9); with K split, whose
+        // partials go through that cache, 3 - 11 and 0 - 5 % faster.  In one
+        // round, K whole, non-temporal ones are faster from both, 2 - 4 %.
+        if (w_bytes < kLastLevelBytes && (m.split_k > 1 || p.pub.workgroups > kCUs)) m.w_stream = false;
         const MediumLaunch ml{m, int(p.pub.workgroups), p.medium_cfg, layout->kind == TL_LAYOUT_TILE, false};
         DecodeLaunch r;
         r.medium = &ml;

@@ -21,6 +21,9 @@ struct MediumParams {
     int bc_mask = 0;
     bool out_bf16 = false;
     int n_tiles = 0;         // column tiles
+    // load weights that no other workgroup reads non-temporally (only where a
+    // K step ends where a line of a weight row does)
+    bool w_stream = false;
     // one weight (num_groups 0): total_rows rows in one tile, K split split_k
     // ways (> 1: fp32 partials at ws, ws_stride floats apart)
     int split_k = 1;

@@ -44,8 +44,9 @@
 // 2048 tokens (32 / 64 / 128 rows per expert) 380 / 586 / 1020 us on the
 // decode kernel's 64-row passes -> 212 / 231 / 265 us; reading the weights
 // once takes 183 us.  Groups of 200 rows, two chunks: 1493 -> 383 us.
-// Non-temporal weight loads, taken when a group's rows
-// fit one tile, are part of that (512 tokens: 228 -> 213 us); with row chunks
+// Non-temporal weight loads, taken when a group's rows fit one tile (and for
+// one weight by the rule at its launch, tl_api.cpp), are part of that (512
+// tokens: 228 -> 213 us; weights of 2 - 200 MB 0 - 10 %); with row chunks
 // that share the weight they cost (8 groups of 256 rows: 158 -> 165 us), and
 // with rows of W that are not whole lines, whose ends two K steps share (96 x
 // 57701 x 1992 row-major: 71.9 -> 78.2 us with them, 70.3 without), as
@@ -140,10 +141,8 @@ __global__ __launch_bounds__(128 * WN) __attribute__((amdgpu_waves_per_eu(2, 2))
 
     // ---- which rows and columns ----
     int nt, split = 0, row0, rows;               // output rows [row0, row0 + rows)
-    // non-temporal weight loads: no other workgroup reads the tile's weight, and
-    // a K step ends where a line of it does
-    const bool lines = TILE || p.K % 64 == 0;
-    bool w_once = lines;
+    // non-temporal weight loads, where no other workgroup reads the tile's weight
+    bool w_once = p.w_stream;
     const uint8_t* W = p.W;
     if constexpr (GROUPED) {
         // units in use: group by group, in a group tile by tile, in a tile
@@ -206,7 +205,7 @@ __global__ __launch_bounds__(128 * WN) __attribute__((amdgpu_waves_per_eu(2, 2))
         const int b0 = int(int64_t(blocks) * chunk / int(chunks)), b1 = int(int64_t(blocks) * (chunk + 1) / int(chunks));
         row0 = r0 + b0 * 32;
         rows = min(r0 + b1 * 32, r1) - row0;
-        w_once = lines && chunks == 1;
+        w_once = p.w_stream && chunks == 1;
         W += int64_t(group) * p.group_stride;
     } else {
         // one weight, all rows in one tile: column tiles, then K splits; each
