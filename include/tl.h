@@ -234,8 +234,8 @@ int tl_unpack(const void* src_tm, void* dst, int64_t rows, int64_t cols, int32_t
  * workgroups, or 128x128 tiles; when 256x256 tiles are fewer than the CUs
  * (and K % 64 == 0, N % 256 == 0), every column takes them with K split, up
  * to 8 ways -- at M <= 128, 128x128 tiles with K split when those are fewer
- * than the CUs (N % 128 == 0).  With M <= 224 in one row of tiles they run on
- * the row-adaptive kernel, which computes only the 32-row blocks that exist;
+ * than the CUs (N % 128 == 0).  With M <= 224 in one row of tiles they mostly
+ * run on the row-adaptive kernel, which computes only the 32-row blocks that exist;
  * above, 192- or 320-row tiles, with at least as many K splits, take the place
  * of 256-row ones where they leave fewer padded rows; see tl_gemm_plan).
  * layout->elem_bytes = 1 means an FP8 weight (OCP E4M3, one

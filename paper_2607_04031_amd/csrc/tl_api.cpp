@@ -183,7 +183,7 @@ struct Plan {
     int lds_tiles = 0;           // > 0: decode with weights and activations staged in LDS, tiles per workgroup
     bool kn_row = false;         // weight stored [K][N] (N contiguous): the transposing decode kernel
     bool kn_wide = false;        // that kernel with 256 columns per workgroup
-    int split_rest = 0;          // prefill: K splits of the tile_m x 256 tiles past n_main (0: 128 x 128 tiles)
+    int split_rest = 0;          // prefill: K splits of the columns past n_main (0: 128 x 128 tiles, whole K)
     bool persist = false;        // prefill: one workgroup per CU walks the main launch's tiles
     bool medium = false;         // all rows in one tile of the row-adaptive kernel
     MediumConfig medium_cfg = MediumConfig::kNarrow;
@@ -592,13 +592,28 @@ int plan_gemm(int64_t M, int64_t N, int64_t K, const tl_layout_desc* d, int32_t 
         // 65 <= M <= 128 (one row of 128-row tiles): 128 x 128 tiles with K
         // split over all the columns in the same way, when they are fewer
         // than the CUs -- no padded rows past 128, against half or more of a
-        // 256-row tile's (row-adaptive kernel, see the end of this function)
+        // 256-row tile's (mostly the row-adaptive kernel, see the end of this
+        // function)
         if (!d->tile_m && !d->tile_n && M > kDecodeMaxM && M <= 128 && N % 128 == 0 && !p.block_row &&
             (!tile || 128 % p.L.br == 0) && N / 128 < kCUs) {
             const int64_t t128 = N / 128;
             const int64_t S = std::min<int64_t>({kCUs / t128, 8, (K + 63) / 64 / 8});
             if (S >= 2) {
-                p.medium = true;
+                // (short K ranges on nearly all the CUs, at 97 rows or more:
+                // the 128 x 128 kernel stays.  From HBM the two are within 4 %,
+                // of a weight that the last level of cache holds the
+                // row-adaptive kernel is 6 - 12 % slower: M = 104, 16000 x 1152
+                // 17.0 us against 19.4; M = 112, 8064 x 2944 18.9 against 20.5,
+                // from HBM 20.6 against 21.3.  At 160 workgroups, 20 steps or
+                // M = 96 it is 2 - 9 % faster from HBM, even to 6 % slower from
+                // the cache)
+                const bool medium = !(M > 96 && t128 * S >= 190 && (K + 63) / 64 <= 16 * S);
+                p.medium = medium;
+                if (!medium) {
+                    p.n_main = 0;                // no main launch: every column splits K
+                    p.split_rest = int(S);
+                    p.persist = false;
+                }
                 p.pub.tile_m = 128;
                 p.pub.tile_n = 128;
                 p.pub.tile_k = int(p.k_unit);
@@ -932,10 +947,12 @@ static int gemm_impl(const void* A, const void* W, const float* scales, void* C,
         // that fits would be read from there by a next call: in more than one
         // round of workgroups plain loads then are 8 - 20 % faster (M = 128,
         // 44544 x 2312: 62.4 -> 47.6 us, 128 x 128 tiles of tl_prefill.hip 46.9)
-        // and 4 - 7 % slower from HBM (61.2 -> 64.3; 67.9); with K split, whose
-        // partials go through that cache, 3 - 11 and 0 - 5 % faster.  In one
-        // round, K whole, non-temporal ones are faster from both, 2 - 4 %.
-        if (w_bytes < kLastLevelBytes && (m.split_k > 1 || p.pub.workgroups > kCUs)) m.w_stream = false;
+        // and 4 - 7 % slower from HBM (61.2 -> 64.3; 67.9).  In one round, K
+        // whole, non-temporal ones are faster from both, 2 - 4 %; with K split
+        // from HBM (layers of 8B / 70B shapes, M = 65 - 128: 116 - 132 against
+        // 123 - 138, 310 - 371 against 318 - 378 us, 0 - 10 % slower from the
+        // cache).
+        if (w_bytes < kLastLevelBytes && p.pub.workgroups > kCUs) m.w_stream = false;
         const MediumLaunch ml{m, int(p.pub.workgroups), p.medium_cfg, layout->kind == TL_LAYOUT_TILE, false};
         DecodeLaunch r;
         r.medium = &ml;

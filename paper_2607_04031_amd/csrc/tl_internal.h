@@ -134,7 +134,7 @@ struct PrefillLaunch {
     int64_t fetch_G = 0;
     // > 1: columns [n_main, N) run as tile_m x 256 tiles with K split this many
     // ways (fp32 partials in ws, M * (N - n_main) floats per split) instead
-    // of 128 x 128 tiles
+    // of 128 x 128 tiles; with tile_m 128 and n_main 0, all as 128 x 128 ones
     int split_rest = 0;
     float* ws = nullptr;
     // columns [0, n_main) with 256 x 256 tiles, bf16 out, M and n_main

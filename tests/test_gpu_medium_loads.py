@@ -1,6 +1,6 @@
 """The row-adaptive kernel on one weight, around the lines of the rule for its
-non-temporal loads: one round of workgroups and one more, K whole and split,
-rows that are whole lines and not; and the ragged columns past 88 rows that stay
+non-temporal loads: one round of workgroups and one more, rows that are whole
+lines and not, K split; and the ragged columns past 88 rows that stay
 on the 128 x 128 kernel where there is more than one round."""
 import pytest
 
